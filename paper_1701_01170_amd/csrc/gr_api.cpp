@@ -160,25 +160,27 @@ struct OffsetsJob {
   const uint32_t* n_f_dev;
   const int32_t* R;
   const int64_t* block_sums;
-  const int64_t* total;
   int32_t* offsets;
   int32_t* rstart;
   int32_t* chunk_start;
   int32_t chunk;
 };
 
-gr_status read_ctrl(gr_ctx* ctx, Ctrl* dev, hipStream_t st, const MlpSelect* sel = nullptr,
-                    const OffsetsJob* pre = nullptr, const PublishExtra* extra = nullptr) {
+// stats: the frontier statistics queued last, added up into the host's copy.
+gr_status read_ctrl(gr_ctx* ctx, Ctrl* dev, hipStream_t st, const StatsSum& stats = StatsSum{},
+                    const MlpSelect* sel = nullptr, const OffsetsJob* pre = nullptr,
+                    const PublishExtra* extra = nullptr) {
   const uint32_t seq = ++ctx->publish_seq;
   const PublishExtra x = extra ? *extra : PublishExtra{};
   if (sel)
-    GR_HIP(launch_publish_select(*sel, dev, ctx->host_ctrl_dev, ctx->publish_flag_dev, seq, st, x));
+    GR_HIP(launch_publish_select(*sel, dev, ctx->host_ctrl_dev, ctx->publish_flag_dev, seq, st, x,
+                                 stats));
   else
-    GR_HIP(launch_publish(dev, ctx->host_ctrl_dev, ctx->publish_flag_dev, seq, st, x));
+    GR_HIP(launch_publish(dev, ctx->host_ctrl_dev, ctx->publish_flag_dev, seq, st, x, stats));
   if (pre)
-    GR_HIP(launch_frontier_offsets(pre->frontier, 0, pre->R, pre->block_sums, pre->total,
-                                   pre->offsets, pre->rstart, pre->chunk_start, pre->chunk, st,
-                                   pre->n_f_dev));
+    GR_HIP(launch_frontier_offsets(pre->frontier, 0, pre->R, pre->block_sums, pre->offsets,
+                                   pre->rstart, pre->chunk_start, pre->chunk, st, pre->n_f_dev,
+                                   /*ready=*/true));
   const auto t0 = std::chrono::steady_clock::now();
   for (uint64_t i = 1;; ++i) {
     if (*ctx->publish_flag == seq) break;
@@ -932,7 +934,7 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
     return MlpSelect{mlp, slot, V, E, n_u, m_u, prev_pull, allowed};
   };
   MlpSelect msel = select_at(sp, V, E, 0);
-  GR_TRY(read_ctrl(ctx, ctrl, st, learned ? &msel : nullptr));
+  GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
 
   Selector sel;
   sel.init(opts, g->V, g->E, pull_ok, /*is_sssp=*/false, ctx->policy_loaded);
@@ -995,7 +997,8 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
       // while tracing, the publication also copies the block's level log
       const PublishExtra lgx{reinterpret_cast<const uint32_t*>(dl.log),
                              reinterpret_cast<uint32_t*>(ctx->host_dlog_dev), 6 * kmax};
-      GR_TRY(read_ctrl(ctx, ctrl, st, learned ? &msel : nullptr, nullptr, tracing ? &lgx : nullptr));
+      GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr, nullptr,
+                       tracing ? &lgx : nullptr));
       const int k = hc->dl_levels;
       if (k > 0) {
         const int64_t* lg = ctx->host_dlog;  // the block's level log (host copy)
@@ -1043,7 +1046,7 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
     if (action == GR_PUSH_LB || action == GR_PUSH_TWC) {
       const int mode = action == GR_PUSH_TWC ? 0 : (n_f < opts.lb_light_threshold ? 1 : 2);
       if (mode == 2)
-        GR_HIP(launch_frontier_offsets(q[cur], n_f, g->R, bsums, &ctrl->m_f[sp], offsets, rstart,
+        GR_HIP(launch_frontier_offsets(q[cur], n_f, g->R, bsums, offsets, rstart,
                                        chunks, chunk, st));
       // canonical parents by an atomic minimum in the push (about one atomic
       // per frontier edge) or by the fix-up scan of the new vertices, which
@@ -1116,18 +1119,22 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
       ulc ^= 1;
       list_ok = true;
     }
-    GR_HIP(launch_bitmap_merge(bm, p, NW, st));
     if (tracing && !opts.trace_steps_off) GR_HIP(hipEventRecord(ctx->ev_b, st));
     rs.action_count[action]++;
+    StatsExtra merge;  // the statistics kernel also merges the bitmap
+    merge.bm = bm;
+    merge.p = p;
+    merge.n_words = NW;
     p ^= 1;
     cur = (cur + 1) % 3;
     sp ^= 1;
     ++level;
     // (the list the next pull level appends to starts empty)
     GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
-                                 &ctrl->q_count[(cur + 1) % 3], &ctrl->ul_count[ulc ^ 1], st));
+                                 &ctrl->q_count[(cur + 1) % 3], &ctrl->ul_count[ulc ^ 1], st,
+                                 merge));
     msel = select_at(sp, V - visited_n, E - visited_m, sel.mode_pull ? 1 : 0);
-    GR_TRY(read_ctrl(ctx, ctrl, st, learned ? &msel : nullptr));
+    GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
     list_n = hc->ul_count[ulc];
     if (tracing) {
       const bool pulled = kernel >= 4 && kernel <= kTraceKernelPullList;
@@ -1299,7 +1306,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
   const bool learned = opts.policy == GR_POLICY_LEARNED && ctx->policy_loaded;
   const float* mlp = static_cast<const float*>(ctx->pool[S_MLP].ptr);
   MlpSelect msel{mlp, sp, V, E, 0, 0, 0, 0x3};
-  GR_TRY(read_ctrl(ctx, ctrl, st, learned ? &msel : nullptr));
+  GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
 
   Selector sel;
   sel.init(opts, V, E, /*pull_ok=*/false, /*is_sssp=*/true, ctx->policy_loaded);
@@ -1323,12 +1330,18 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
   const bool lb_likely = (double)E / (double)V >= (double)opts.lb_min_avg_degree;
   bool offsets_ready = false;
   auto next_frontier = [&]() -> gr_status {
+    StatsExtra keep;  // the degrees and row starts for the scan queued below
+    if (lb_likely) {
+      keep.deg = offsets;
+      keep.rstart = rstart;
+    }
     GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
-                                 &ctrl->q_count[(cur + 1) % 3], nullptr, st));
+                                 &ctrl->q_count[(cur + 1) % 3], nullptr, st, keep));
     msel.sp = sp;
-    const OffsetsJob pre{q[cur], &ctrl->q_count[cur], g->R, bsums, &ctrl->m_f[sp], offsets,
+    const OffsetsJob pre{q[cur], &ctrl->q_count[cur], g->R, bsums, offsets,
                          rstart, chunks, chunk};
-    GR_TRY(read_ctrl(ctx, ctrl, st, learned ? &msel : nullptr, lb_likely ? &pre : nullptr));
+    GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr,
+                     lb_likely ? &pre : nullptr));
     offsets_ready = lb_likely;
     if (use_pq) far_n = hc->far_count[pq.fc];
     return GR_OK;
@@ -1374,7 +1387,8 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
       // while tracing, the publication also copies the block's level log
       const PublishExtra lgx{reinterpret_cast<const uint32_t*>(dl.log),
                              reinterpret_cast<uint32_t*>(ctx->host_dlog_dev), 6 * kmax};
-      GR_TRY(read_ctrl(ctx, ctrl, st, learned ? &msel : nullptr, nullptr, tracing ? &lgx : nullptr));
+      GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr, nullptr,
+                       tracing ? &lgx : nullptr));
       const int k = hc->dl_levels;
       if (use_pq) {
         pq.T = hc->pq_T[k & 1];
@@ -1430,7 +1444,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
       const int mode = action == GR_PUSH_TWC ? 0 : (n_f < opts.lb_light_threshold ? 1 : 2);
       kernel = mode;
       if (mode == 2 && !offsets_ready)
-        GR_HIP(launch_frontier_offsets(q[cur], n_f, g->R, bsums, &ctrl->m_f[sp], offsets, rstart,
+        GR_HIP(launch_frontier_offsets(q[cur], n_f, g->R, bsums, offsets, rstart,
                                        chunks, chunk, st));
       if (tracing) GR_HIP(hipEventRecord(ctx->ev_k0, st));
       if (m_f >= V / kSsspMarksDivisor) {
@@ -1584,7 +1598,6 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
     GR_HIP(hipMemcpyAsync(src_dev, srcs.data(), sizeof(int32_t) * 2 * kk, hipMemcpyHostToDevice, st));
     GR_HIP(hipMemcpyAsync(qA, uniq.data(), sizeof(int32_t) * uniq.size(), hipMemcpyHostToDevice, st));
     GR_HIP(launch_fill_u32(&ctrl->q_count[0], 1, (uint32_t)uniq.size(), st));
-    GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(&ctrl->m_f[0]), 8, 0u, st));  // m_f, max_deg
     GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(&ctrl->ms_pairs), 4, 0u, st));
     GR_HIP(launch_ms_seed(src_dev, src_dev + kk, kk, visit, front[0], dpass, V, g->R, ctrl, st));
     int cur = 0, fc = 0, sp = 0, level = 0;
@@ -1599,7 +1612,7 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
                                  &ctrl->q_count[(cur + 1) % 3], nullptr, st));
     MlpSelect msel = select_at(sp);
     // (the read-back also keeps the host source vectors alive for the copies)
-    GR_TRY(read_ctrl(ctx, ctrl, st, learned ? &msel : nullptr));
+    GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
     int64_t n_a = hc->n_f[sp], m_a = hc->m_f[sp];
     while (n_a > 0 && (opts.max_iterations <= 0 || level < opts.max_iterations)) {
       // heuristic: pull (every vertex with unreached source bits ORs its
@@ -1655,7 +1668,7 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
                                                  st));
         prev_pull = false;
         msel = select_at(sp);
-        GR_TRY(read_ctrl(ctx, ctrl, st, learned ? &msel : nullptr));
+        GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
         const int kd = hc->dl_levels;
         if (kd == kmax) dl_len = std::min(2 * dl_len, kDlMaxLevels);
         else if (2 * kd < kmax) dl_len = std::max(dl_len / 2, kDlFirstLen);
@@ -1681,7 +1694,7 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
         const int mode = action == GR_PUSH_TWC ? 0 : (n_a < opts.lb_light_threshold ? 1 : 2);
         kernel = mode;
         if (mode == 2)
-          GR_HIP(launch_frontier_offsets(q[cur], n_a, g->R, bsums, &ctrl->m_f[sp], offsets, rstart,
+          GR_HIP(launch_frontier_offsets(q[cur], n_a, g->R, bsums, offsets, rstart,
                                          chunks, chunk, st));
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k0, st));
         GR_HIP(launch_ms_push(mode, q[cur], offsets, rstart, chunks, n_a, m_a, g->R, g->C,
@@ -1705,7 +1718,7 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
       GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
                                    &ctrl->q_count[(cur + 1) % 3], nullptr, st));
       msel = select_at(sp);
-      GR_TRY(read_ctrl(ctx, ctrl, st, learned ? &msel : nullptr));
+      GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
       if (tracing)
         GR_TRY(record_trace(ctx, opts_in, lf, action, kernel, hc->n_f[sp],
                             StepWork{pull ? V : n_a, pull ? E : m_a}));
@@ -1824,14 +1837,13 @@ extern "C" gr_status gr_sssp_multi(gr_ctx* ctx, const gr_graph* g, const int32_t
     GR_HIP(hipMemcpyAsync(src_dev, srcs.data(), sizeof(int32_t) * 2 * kk, hipMemcpyHostToDevice, st));
     GR_HIP(hipMemcpyAsync(qA, uniq.data(), sizeof(int32_t) * uniq.size(), hipMemcpyHostToDevice, st));
     GR_HIP(launch_fill_u32(&ctrl->q_count[0], 1, (uint32_t)uniq.size(), st));
-    GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(&ctrl->m_f[0]), 8, 0u, st));  // m_f, max_deg
     GR_HIP(launch_msssp_init(keys, KS, amask, nmask, fmask, relaxed, V, src_dev, kk, st));
     GR_HIP(launch_fill_u32(&ctrl->far_count[0], 2, 0u, st));
     int cur = 0, sp = 0, it = 0, pile = 0;
     uint32_t T = (uint32_t)opts.sssp_delta;
     GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
                                  &ctrl->q_count[(cur + 1) % 3], &ctrl->q_count[(cur + 2) % 3], st));
-    GR_TRY(read_ctrl(ctx, ctrl, st));  // also keeps the host source vectors alive for the copies
+    GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}));  // also keeps the host source vectors alive for the copies
     int64_t n_f = hc->n_f[sp], m_f = hc->m_f[sp], far_n = 0;
     while ((n_f > 0 || far_n > 0) && (opts.max_iterations <= 0 || it < opts.max_iterations)) {
       if (n_f == 0) {
@@ -1846,7 +1858,7 @@ extern "C" gr_status gr_sssp_multi(gr_ctx* ctx, const gr_graph* g, const int32_t
         T = T1;
         pile ^= 1;
       } else {
-        GR_HIP(launch_frontier_offsets(q[cur], n_f, g->R, bsums, &ctrl->m_f[sp], offsets, rstart,
+        GR_HIP(launch_frontier_offsets(q[cur], n_f, g->R, bsums, offsets, rstart,
                                        chunks, chunk, st));
         const MsFar far{fmask, use_pq ? piles + (int64_t)pile * V : nullptr, &ctrl->far_count[pile],
                         T};
@@ -1866,7 +1878,7 @@ extern "C" gr_status gr_sssp_multi(gr_ctx* ctx, const gr_graph* g, const int32_t
       GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
                                    &ctrl->q_count[(cur + 1) % 3], &ctrl->q_count[(cur + 2) % 3],
                                    st));
-      GR_TRY(read_ctrl(ctx, ctrl, st));
+      GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}));
       n_f = hc->n_f[sp];
       m_f = hc->m_f[sp];
       far_n = use_pq ? hc->far_count[pile] : 0;
@@ -1997,7 +2009,6 @@ extern "C" gr_status gr_bc(gr_ctx* ctx, const gr_graph* g, const int32_t* source
     GR_HIP(hipMemcpyAsync(tab_dev, tab.data(), sizeof(int64_t) * tab.size(), hipMemcpyHostToDevice,
                           st));
     GR_HIP(launch_bc_scatter(depth, V, L, lvl_n + L, levels, st));
-    GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(&ctrl->m_f[0]), 8, 0u, st));  // m_f, max_deg
     sp = 0;
     // the LB maps of all levels at once: one degree scan over the reached
     // vertices in level order (its chunk output is not used: the chunk size
@@ -2005,7 +2016,7 @@ extern "C" gr_status gr_bc(gr_ctx* ctx, const gr_graph* g, const int32_t* source
     // (the last level's cursor ends at n_r)
     GR_HIP(launch_frontier_stats(levels, lvl_n + L + L - 1, g->R, bsums, ctrl, sp, nullptr, nullptr,
                                  st));
-    GR_HIP(launch_frontier_offsets(levels, n_r, g->R, bsums, &ctrl->m_f[sp], all_offs, all_rstart,
+    GR_HIP(launch_frontier_offsets(levels, n_r, g->R, bsums, all_offs, all_rstart,
                                    chunks, 1 << 30, st));
     sp ^= 1;
     GR_HIP(launch_bc_chunk_map(levels, depth, n_r, all_offs, tab_dev, L, chunk, bc_chunks, st));

@@ -90,12 +90,12 @@ enum Slot : int {
 
 // Device control block.  Counters used for appends are 32-bit; sums are
 // 64-bit.  Frontier statistics use two slots selected by the parity of the
-// statistics call, so each call can clear the slot the next one accumulates in.
+// statistics call.
 struct Ctrl {
   uint32_t q_count[3];      // frontier queue lengths (three rotating queues)
   uint32_t cand_count;      // BFS idempotent advance: candidate list length (may exceed its capacity)
-  int64_t m_f[2];           // sum of frontier degrees
-  int64_t max_deg[2];       // largest frontier degree
+  int64_t m_f[2];           // sum of frontier degrees (host copy only: added up as it is published)
+  int64_t max_deg[2];       // largest frontier degree (host copy only)
   int64_t n_f[2];           // frontier size as seen by the statistics kernel
   int64_t inspected;        // pull: neighbours scanned (accumulated)
   int64_t reached_edges;    // sum of degrees over reached vertices (end of run)
@@ -216,12 +216,32 @@ hipError_t launch_graph_stats(const int32_t* R, const uint32_t* W, int64_t V, in
                               int64_t* out2, hipStream_t st);
 
 // frontier statistics and scan
+constexpr int kStatsGrid = 512;  // blocks of the statistics and scan kernels
 int stats_grid();
-// Degree sum / max / size of the frontier (size read on the device), into slot
-// `parity` of the control block; clears the other slot and the two counters.
+// What a statistics call does on the way: keep every entry's degree and row
+// start for the degree scan; merge the BFS bitmap (live |= old: live = depth <=
+// d + 1 after level d).  Null pointers: not wanted.
+struct StatsExtra {
+  int32_t* deg = nullptr;
+  int32_t* rstart = nullptr;
+  uint32_t* bm = nullptr;
+  int p = 0;
+  int64_t n_words = 0;
+};
+// Degree sum / max of the frontier (size read on the device) per block into
+// block_sums[kStatsGrid], its size into slot `parity` of the control block;
+// clears the two counters.  The publication of the control block adds the
+// blocks up (StatsSum).
 hipError_t launch_frontier_stats(const int32_t* frontier, const uint32_t* n_f_dev, const int32_t* R,
                                  int64_t* block_sums, Ctrl* ctrl, int parity, uint32_t* zero_a,
-                                 uint32_t* zero_b, hipStream_t st);
+                                 uint32_t* zero_b, hipStream_t st,
+                                 const StatsExtra& extra = StatsExtra{});
+// The statistics a publication adds up into slot `slot` of the host's control
+// block (block_sums null: none).
+struct StatsSum {
+  const int64_t* block_sums = nullptr;
+  int slot = 0;
+};
 // The three rotating frontier queues.
 struct Queues3 {
   int32_t* q[3];
@@ -234,11 +254,12 @@ hipError_t launch_frontier_stats_after_block(const Queues3& qs, int cur0, const 
                                              hipStream_t st);
 // n_f_dev, when not null, is the frontier size on the device (n_f is then
 // ignored), so the kernel can be queued before the host knows the size.
+// ready: the statistics call kept the degrees in offsets[] and the row starts
+// in rstart[] (StatsExtra).
 hipError_t launch_frontier_offsets(const int32_t* frontier, int64_t n_f, const int32_t* R,
-                                   const int64_t* block_sums, const int64_t* total,
-                                   int32_t* offsets, int32_t* rstart, int32_t* chunk_start,
-                                   int32_t chunk, hipStream_t st,
-                                   const uint32_t* n_f_dev = nullptr);
+                                   const int64_t* block_sums, int32_t* offsets, int32_t* rstart,
+                                   int32_t* chunk_start, int32_t chunk, hipStream_t st,
+                                   const uint32_t* n_f_dev = nullptr, bool ready = false);
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t value, hipStream_t st);
 // copy *src into host-visible memory, then store seq to *flag (system scope)
 // Extra words a publication copies to host memory before its fence (a block
@@ -249,7 +270,8 @@ struct PublishExtra {
   int n_words = 0;
 };
 hipError_t launch_publish(const Ctrl* src, Ctrl* host_dst, uint32_t* host_flag, uint32_t seq,
-                          hipStream_t st, const PublishExtra& extra = PublishExtra{});
+                          hipStream_t st, const PublishExtra& extra = PublishExtra{},
+                          const StatsSum& stats = StatsSum{});
 // out[c] = in[inv[c]] for the depth and (nullable) parent arrays (inv: caller
 // id -> traversal id)
 hipError_t launch_permute_out(const int32_t* inv, int64_t V, const int32_t* depth_in,
@@ -393,8 +415,6 @@ hipError_t launch_msssp_finalize(const unsigned long long* keys, int KS, int32_t
                                  const int32_t* R, int64_t V, uint32_t* dist, int32_t* pred,
                                  const int32_t* perm, const int32_t* src_orig_dev,
                                  int64_t* reached_edges, hipStream_t st);
-// live |= old (live = depth <= d + 1 after level d)
-hipError_t launch_bitmap_merge(uint32_t* bm, int p, int64_t n_words, hipStream_t st);
 
 // multi-source BFS (64-bit source masks per vertex); depth / parent are the
 // caller's [k][V] arrays in caller ids (perm nullable)
@@ -474,7 +494,7 @@ struct MlpSelect {
 // to host memory as launch_publish does; one kernel for both.
 hipError_t launch_publish_select(const MlpSelect& m, Ctrl* ctrl, Ctrl* host_dst,
                                  uint32_t* host_flag, uint32_t seq, hipStream_t st,
-                                 const PublishExtra& extra = PublishExtra{});
+                                 const PublishExtra& extra, const StatsSum& stats);
 
 // Device-predicated level blocks (iteration control): up to kDlMaxLevels
 // push levels are enqueued back to back; each level kernel first decides on

@@ -9,6 +9,7 @@
 #include "gr_internal.h"
 #include "k_common.h"
 #include "k_mlp.h"
+#include "k_stats.h"
 
 namespace gr {
 
@@ -200,17 +201,19 @@ __global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, const float
 // network runs first (its outputs go to the device control block and, taken
 // from LDS, into the host copy), then every word is copied to host memory,
 // ordered at system scope, and one thread releases the sequence number.
-__global__ __launch_bounds__(128) void k_publish_select(MlpSelect m, Ctrl* __restrict__ ctrl,
-                                                        uint32_t* __restrict__ dst, uint32_t* flag,
-                                                        uint32_t seq, PublishExtra x) {
+__global__ __launch_bounds__(kPublishBlock) void k_publish_select(
+    MlpSelect m, Ctrl* __restrict__ ctrl, uint32_t* __restrict__ dst, uint32_t* flag, uint32_t seq,
+    PublishExtra x, StatsSum st) {
+  __shared__ StatsTotal s_t;
   __shared__ float s_p[kNP];
   __shared__ float s_x[kIn], s_h1[kH], s_h2[kH], s_y[kOut];
   __shared__ uint32_t s_dec[kOut + 1];
   // the parameters are staged in LDS with one coalesced burst: read layer by
   // layer from memory, each layer would wait for its own round trip
   for (int i = threadIdx.x; i < kNP; i += blockDim.x) s_p[i] = m.params[i];
+  stats_total(st, &s_t);
   if (threadIdx.x < kIn) {
-    const int64_t n_f = ctrl->n_f[m.sp], m_f = ctrl->m_f[m.sp];
+    const int64_t n_f = ctrl->n_f[m.sp], m_f = (int64_t)s_t.w[1] << 32 | s_t.w[0];
     int64_t nub = m.n_u_before, mub = m.m_u_before;
     if (m.after_block) {
       const int k = ctrl->dl_levels;
@@ -227,7 +230,7 @@ __global__ __launch_bounds__(128) void k_publish_select(MlpSelect m, Ctrl* __res
     // builds no unvisited list, so the single-source meaning does not apply)
     s_x[threadIdx.x] = m.ms_k > 0 && threadIdx.x == kIn - 1
                            ? mlp_feat((double)m.ms_k)
-                           : mlp_feature(threadIdx.x, n_f, m_f, n_u, m_u, ctrl->max_deg[m.sp], m.V,
+                           : mlp_feature(threadIdx.x, n_f, m_f, n_u, m_u, s_t.w[2], m.V,
                                          m.E, m.prev_pull);
   }
   const int best = mlp_argmin(s_p, s_x, s_h1, s_h2, s_y, m.allowed);
@@ -249,9 +252,11 @@ __global__ __launch_bounds__(128) void k_publish_select(MlpSelect m, Ctrl* __res
     uint32_t w;
     if (i >= kPred && i < kPred + kOut) w = s_dec[i - kPred];
     else if (i == kAction) w = s_dec[kOut];
+    else if (stats_word(st.slot, i)) continue;
     else w = src[i];
     dst[i] = w;
   }
+  if (threadIdx.x < 4) dst[stats_word_at(st.slot, threadIdx.x)] = s_t.w[threadIdx.x];
   for (int i = threadIdx.x; i < x.n_words; i += blockDim.x) x.dst[i] = x.src[i];
   __threadfence_system();
   __syncthreads();
@@ -288,10 +293,10 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n, floa
 
 hipError_t launch_publish_select(const MlpSelect& m, Ctrl* ctrl, Ctrl* host_dst,
                                  uint32_t* host_flag, uint32_t seq, hipStream_t st,
-                                 const PublishExtra& extra) {
+                                 const PublishExtra& extra, const StatsSum& stats) {
   static_assert(sizeof(Ctrl) % 4 == 0, "control block is copied as 32-bit words");
-  k_publish_select<<<1, 128, 0, st>>>(m, ctrl, reinterpret_cast<uint32_t*>(host_dst), host_flag,
-                                      seq, extra);
+  k_publish_select<<<1, kPublishBlock, 0, st>>>(m, ctrl, reinterpret_cast<uint32_t*>(host_dst),
+                                                host_flag, seq, extra, stats);
   return hipGetLastError();
 }
 

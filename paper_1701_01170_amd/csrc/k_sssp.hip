@@ -678,8 +678,6 @@ __global__ __launch_bounds__(256) void k_sssp_init(unsigned long long* __restric
     ctrl->q_count[2] = 0;
     ctrl->inspected = 0;
     ctrl->reached_edges = 0;
-    ctrl->m_f[0] = ctrl->m_f[1] = 0;
-    ctrl->max_deg[0] = ctrl->max_deg[1] = 0;
   }
 }
 
