@@ -1560,10 +1560,17 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
   Ctrl* hc = ctx->host_ctrl;
   int32_t* q[3] = {qA, qB, qC};
 
+  // depth planes and parent rows of a pass (see k_multi.hip); without the
+  // memory for them the caller's arrays are written directly
+  int kp_log = 0;
+  while ((1 << kp_log) < std::min<int32_t>(k, 64)) ++kp_log;
+  u64* planes = nullptr;
+  uint32_t* prow = nullptr;
+  if (pool_typed(ctx, S_MS_PLANES, (size_t)V * kMsPlanes, &planes) != GR_OK) planes = nullptr;
+  if (planes && parent && pool_typed(ctx, S_MS_PROW, (size_t)V << kp_log, &prow) != GR_OK)
+    planes = nullptr;
+
   GR_HIP(hipEventRecord(ctx->ev_start, st));
-  GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(depth), (int64_t)k * V, 0xffffffffu, st));
-  if (parent)
-    GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(parent), (int64_t)k * V, 0xffffffffu, st));
   GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(&ctrl->reached_edges), 2, 0u, st));
   gr_run_stats rs{};
   int64_t inspected = 0;
@@ -1578,6 +1585,8 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
   const int64_t dl_max_m = opts.device_max_edges > 0 ? opts.device_max_edges : kDlDefaultMaxEdges;
   const double dl_do_a = opts.policy == GR_POLICY_FIXED ? -1.0 : (double)opts.do_a;
   const int dl_blocks = ctx->cu_count > 0 ? ctx->cu_count : 256;
+  const bool short_rows = g->max_degree <= kDpMaxDegree;
+  const int64_t dl_max_n = short_rows ? kDpMaxN : kDlMaxN;
   int dl_len = kDlFirstLen;
   for (int32_t p0 = 0; p0 < k; p0 += 64) {
     const int32_t kk = std::min<int32_t>(64, k - p0);
@@ -1593,13 +1602,30 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
     std::vector<int32_t> uniq(srcs.begin(), srcs.begin() + kk);
     std::sort(uniq.begin(), uniq.end());
     uniq.erase(std::unique(uniq.begin(), uniq.end()), uniq.end());
-    for (u64* m : {visit, front[0], front[1], next})
-      GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(m), 2 * V, 0u, st));
+    MsOut out;
+    out.planes = planes;
+    out.prow = prow;
+    out.kp_log = kp_log;
+    out.depth = dpass;
+    out.parent = ppass;
+    if (!planes) {
+      GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(dpass), (int64_t)kk * V, 0xffffffffu, st));
+      if (ppass)
+        GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(ppass), (int64_t)kk * V, 0xffffffffu, st));
+    }
     GR_HIP(hipMemcpyAsync(src_dev, srcs.data(), sizeof(int32_t) * 2 * kk, hipMemcpyHostToDevice, st));
     GR_HIP(hipMemcpyAsync(qA, uniq.data(), sizeof(int32_t) * uniq.size(), hipMemcpyHostToDevice, st));
-    GR_HIP(launch_fill_u32(&ctrl->q_count[0], 1, (uint32_t)uniq.size(), st));
-    GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(&ctrl->ms_pairs), 4, 0u, st));
-    GR_HIP(launch_ms_seed(src_dev, src_dev + kk, kk, visit, front[0], dpass, V, g->R, ctrl, st));
+    GR_HIP(launch_ms_init(visit, front[0], front[1], next, out, V, (int32_t)uniq.size(), ctrl, st));
+    GR_HIP(launch_ms_seed(src_dev, src_dev + kk, kk, visit, front[0], planes ? nullptr : dpass, V,
+                          g->R, ctrl, st));
+    // the next depth no longer fits the planes: write out what there is and go
+    // on in the caller's arrays
+    auto leave_planes = [&]() -> gr_status {
+      GR_HIP(launch_ms_output(visit, out, kk, g->perm ? g->inv : nullptr, V, st));
+      out.planes = nullptr;
+      return GR_OK;
+    };
+    constexpr int kPlaneDepth = (1 << kMsPlanes) - 1;  // largest depth the planes hold
     int cur = 0, fc = 0, sp = 0, level = 0;
     bool prev_pull = false;
     // the network's inputs for the frontier measured at slot `slot`
@@ -1631,7 +1657,7 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
         if (c >= 0 && c < 4 && c != h && hc->pred[c] + opts.learned_margin < hc->pred[h]) action = c;
         // as in gr_bfs: a push level that fits a device block stays a push
         // (the network was trained on levels with one round trip each)
-        if (dl_on && n_a <= kDlMaxN && m_a <= dl_max_m && h < GR_PULL_TWC && action >= GR_PULL_TWC)
+        if (dl_on && n_a <= dl_max_n && m_a <= dl_max_m && h < GR_PULL_TWC && action >= GR_PULL_TWC)
           action = h;
       }
       LevelFeatures lf{};
@@ -1646,22 +1672,27 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
       lf.prev_pull = prev_pull ? 1 : 0;
       lf.ms_k = kk;
       const bool pull = action >= GR_PULL_TWC;
-      if (dl_on && !pull && n_a <= kDlMaxN && m_a <= dl_max_m) {
+      if (out.planes && level >= kPlaneDepth) GR_TRY(leave_planes());
+      if (dl_on && !pull && n_a <= dl_max_n && m_a <= dl_max_m) {
         // a block of device-predicated push levels, one read-back per block;
         // its first level is the one just decided, the others follow the
-        // heuristic's push test on the device
+        // heuristic's push test on the device (a network that pushes where the
+        // heuristic would pull keeps pushing through the block)
+        const double blk_do_a = h >= GR_PULL_TWC ? -1.0 : dl_do_a;
         int kmax = dl_len;
         if (opts.max_iterations > 0) kmax = std::min(kmax, opts.max_iterations - level);
-        GR_HIP(launch_dl_begin(ctrl, cur, 0, 0, 0u, 0, 0, st));
+        if (out.planes) kmax = std::min(kmax, kPlaneDepth - level);
+        GR_HIP(launch_dl_begin(ctrl, cur, 0, 0, 0u, 0, 0, st, m_a));
         for (int i = 0; i < kmax; ++i) {
           const int qc = (cur + i) % 3;
           const int fi = fc ^ (i & 1);
-          DlArgs da{g->R, g->C, q[qc], q[(qc + 1) % 3], qc, i, kDlMaxN, dl_max_m, E, dl_do_a, V,
+          DlArgs da{g->R, g->C, q[qc], q[(qc + 1) % 3], qc, i, dl_max_n, dl_max_m, E, blk_do_a, V,
                     nullptr, ctrl};
           da.edges_vs_all = 1;
-          const MsLevel ml{g->R, g->C, front[fi], front[fi ^ 1], visit, next, dpass, ppass,
+          const MsLevel ml{g->R, g->C, front[fi], front[fi ^ 1], visit, next, out,
                            g->perm, V, level + i + 1};
-          GR_HIP(launch_ms_dlevel(da, ml, dl_blocks, std::min<int64_t>(V, dl_max_m), st));
+          GR_HIP(launch_ms_dlevel(da, ml, short_rows, dl_blocks, std::min<int64_t>(V, dl_max_m),
+                                  st));
         }
         sp ^= 1;
         GR_HIP(launch_frontier_stats_after_block(Queues3{{qA, qB, qC}}, cur, g->R, bsums, ctrl, sp,
@@ -1687,8 +1718,10 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
       if (tracing && !opts.trace_steps_off) GR_HIP(hipEventRecord(ctx->ev_a, st));
       if (pull) {
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k0, st));
-        GR_HIP(launch_ms_pull(V, g->R, g->C, front[fc], visit, full, next, q[(cur + 1) % 3],
-                              &ctrl->q_count[(cur + 1) % 3], ppass, g->perm, st));
+        // (the degree scan's arrays are free during a pull: they hold its row lists)
+        GR_HIP(launch_ms_pull(V, E, g->max_degree, g->R, g->C, front[fc], visit, full, next,
+                              q[(cur + 1) % 3], &ctrl->q_count[(cur + 1) % 3], out, g->perm, offsets,
+                              rstart, ctrl->ms_big, st));
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k1, st));
       } else {
         const int mode = action == GR_PUSH_TWC ? 0 : (n_a < opts.lb_light_threshold ? 1 : 2);
@@ -1698,17 +1731,16 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
                                          chunks, chunk, st));
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k0, st));
         GR_HIP(launch_ms_push(mode, q[cur], offsets, rstart, chunks, n_a, m_a, g->R, g->C,
-                              front[fc], visit, next, q[(cur + 1) % 3], &ctrl->q_count[(cur + 1) % 3], adv,
-                              st));
+                              front[fc], visit, next, out, V, g->perm, q[(cur + 1) % 3],
+                              &ctrl->q_count[(cur + 1) % 3], adv, st));
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k1, st));
       }
       rs.action_count[action]++;
       inspected += pull ? E : m_a;
-      // a pull level has written its parents already
-      GR_HIP(launch_ms_finalize(q[(cur + 1) % 3], &ctrl->q_count[(cur + 1) % 3], pull ? V : std::min(V, m_a),
-                                g->R, g->C, front[fc], front[fc ^ 1], visit, next, dpass,
-                                pull ? nullptr : ppass, g->perm, V, level + 1, ctrl, st));
-      GR_HIP(launch_ms_clear(q[cur], &ctrl->q_count[cur], n_a, front[fc], st));
+      GR_HIP(launch_ms_finalize(q[(cur + 1) % 3], &ctrl->q_count[(cur + 1) % 3],
+                                pull ? V : std::min(V, m_a), q[cur], &ctrl->q_count[cur], n_a, g->R,
+                                front[fc], front[fc ^ 1], visit, next, out, g->perm, V, level + 1,
+                                ctrl, st));
       if (tracing && !opts.trace_steps_off) GR_HIP(hipEventRecord(ctx->ev_b, st));
       prev_pull = pull;
       fc ^= 1;
@@ -1726,6 +1758,7 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
       m_a = hc->m_f[sp];
     }
     max_levels = std::max(max_levels, level);
+    if (out.planes) GR_TRY(leave_planes());
     GR_HIP(launch_ms_teps(visit, g->R, V, &ctrl->reached_edges, st));
   }
   GR_HIP(hipEventRecord(ctx->ev_stop, st));

@@ -85,6 +85,8 @@ enum Slot : int {
   S_MS_AMASK,      // batched SSSP: sources a frontier vertex is active for [V]
   S_MS_NMASK,      // batched SSSP: sources whose distance dropped this iteration [V]
   S_MS_FMASK,      // batched SSSP: pairs waiting on the far pile [V]
+  S_MS_PLANES,     // batched BFS: depth bit planes [V * kMsPlanes]
+  S_MS_PROW,       // batched BFS: parent rows [V * sources, rounded up to a power of two]
   S_NSLOTS
 };
 
@@ -103,12 +105,14 @@ struct Ctrl {
   float pred[4];            // the network's predicted log2 step times (disallowed: +inf)
   int32_t pad0;
   uint32_t ul_count[2];     // BFS pull: lengths of the two unvisited lists
-  uint32_t pad3[6];
+  uint32_t ms_big[2];       // batched BFS pull: rows listed for the wavefront / workgroup tier
+  uint32_t pad3[4];
   // device-predicated level blocks (iteration control without host round trips)
   int32_t dl_levels;        // levels of the current block that ran
   int32_t dl_stop;          // a level of the block declined to run
   int64_t dl_vm[2];         // degree sum of the vertices reached before the current frontier
   int64_t dl_vn[2];         // number of vertices reached before the current frontier
+  int64_t dl_mf[2];         // edges of the current frontier (k_dpush levels)
   // SSSP two-level priority queue (near / far piles); [2] slots alternate by
   // level inside a device-predicated block
   uint32_t pq_T[2];         // near threshold
@@ -421,32 +425,54 @@ hipError_t launch_msssp_finalize(const unsigned long long* keys, int KS, int32_t
 hipError_t launch_ms_seed(const int32_t* src_dev, const int32_t* src_orig_dev, int32_t k,
                           unsigned long long* visit, unsigned long long* front, int32_t* depth,
                           int64_t V, const int32_t* R, Ctrl* ctrl, hipStream_t st);
+// Where a pass's results go while it runs.  planes != null: depths as bit planes
+// ([V][kMsPlanes] words, depths below 1 << kMsPlanes) and parents in rows of
+// 1 << kp_log words (prow, null when not wanted), turned into the caller's
+// arrays by launch_ms_output; planes == null: written to the caller's arrays
+// (depth, parent: [source][vertex]) as they are found.
+constexpr int kMsPlanes = 4;
+struct MsOut {
+  unsigned long long* planes = nullptr;
+  uint32_t* prow = nullptr;
+  int kp_log = 0;
+  int32_t* depth = nullptr;
+  int32_t* parent = nullptr;
+};
+hipError_t launch_ms_init(unsigned long long* visit, unsigned long long* f0, unsigned long long* f1,
+                          unsigned long long* next, const MsOut& o, int64_t V, int32_t n_src,
+                          Ctrl* ctrl, hipStream_t st);
 hipError_t launch_ms_push(int mode, const int32_t* active, const int32_t* offsets,
                           const int32_t* rstart, const int32_t* chunk_start, int64_t n_a,
                           int64_t m_a, const int32_t* R, const int32_t* C,
                           const unsigned long long* front, const unsigned long long* visit,
+                          unsigned long long* next, const MsOut& o, int64_t V, const int32_t* perm,
+                          int32_t* touched, uint32_t* n_touched, const AdvCfg& cfg, hipStream_t st);
+// The pull writes the parents of the pairs it reaches.  mid_q, hub_q: [V] lists
+// of the longer rows, n_big[2] their counters (zero before; launch_ms_finalize
+// zeroes them again).
+hipError_t launch_ms_pull(int64_t V, int64_t E, int64_t max_degree, const int32_t* R,
+                          const int32_t* C, const unsigned long long* front,
+                          const unsigned long long* visit, unsigned long long full,
                           unsigned long long* next, int32_t* touched, uint32_t* n_touched,
-                          const AdvCfg& cfg, hipStream_t st);
-// pull with parent nullable: when given, the pull writes the parents of the
-// vertices it reaches (the finalize of that level then gets parent = nullptr)
-hipError_t launch_ms_pull(int64_t V, const int32_t* R, const int32_t* C,
-                          const unsigned long long* front, const unsigned long long* visit,
-                          unsigned long long full, unsigned long long* next, int32_t* touched,
-                          uint32_t* n_touched, int32_t* parent, const int32_t* perm,
-                          hipStream_t st);
+                          const MsOut& o, const int32_t* perm, int32_t* mid_q, int32_t* hub_q,
+                          uint32_t* n_big, hipStream_t st);
+// The touched vertices' masks and depths, the masks of the level's frontier
+// (cur_q, at most max_cur entries) cleared.
 hipError_t launch_ms_finalize(const int32_t* touched, const uint32_t* n_touched, int64_t max_n,
-                              const int32_t* R, const int32_t* C, const unsigned long long* front,
+                              const int32_t* cur_q, const uint32_t* n_cur, int64_t max_cur,
+                              const int32_t* R, unsigned long long* front_cur,
                               unsigned long long* front_next, unsigned long long* visit,
-                              unsigned long long* next, int32_t* depth, int32_t* parent,
-                              const int32_t* perm, int64_t V, int32_t next_depth, Ctrl* ctrl,
-                              hipStream_t st);
-hipError_t launch_ms_clear(const int32_t* list, const uint32_t* n, int64_t max_n,
-                           unsigned long long* front, hipStream_t st);
+                              unsigned long long* next, const MsOut& o, const int32_t* perm,
+                              int64_t V, int32_t next_depth, Ctrl* ctrl, hipStream_t st);
+// The caller's [k][V] depth / parent rows from the planes and parent rows
+// (inv, nullable: caller id -> traversal id).
+hipError_t launch_ms_output(const unsigned long long* visit, const MsOut& o, int32_t k,
+                            const int32_t* inv, int64_t V, hipStream_t st);
 struct DlArgs;
 // One device-predicated level of the batched BFS (small push levels): the
-// expansion as a k_dstep, then finalize and clear, both skipping when a level
-// of the block declined (ctrl->dl_stop).  front_cur / front_next alternate by
-// level; depth / parent are the pass's output rows.
+// expansion as a k_dstep, then finalize, which skips when a level of the block
+// declined (ctrl->dl_stop).  front_cur / front_next alternate by
+// level.
 struct MsLevel {
   const int32_t* R;
   const int32_t* C;
@@ -454,14 +480,15 @@ struct MsLevel {
   unsigned long long* front_next;
   unsigned long long* visit;
   unsigned long long* next;
-  int32_t* depth;
-  int32_t* parent;
+  MsOut out;
   const int32_t* perm;
   int64_t V;
   int32_t next_depth;
 };
-hipError_t launch_ms_dlevel(const DlArgs& a, const MsLevel& m, int n_blocks, int64_t max_touched,
-                            hipStream_t st);
+// short_rows: no row of the graph is longer than kDpMaxDegree (the expansion is
+// then a k_dpush, and finalize leaves the next frontier's edge count).
+hipError_t launch_ms_dlevel(const DlArgs& a, const MsLevel& m, bool short_rows, int n_blocks,
+                            int64_t max_touched, hipStream_t st);
 hipError_t launch_ms_teps(const unsigned long long* visit, const int32_t* R, int64_t V, int64_t* out,
                           hipStream_t st);
 
@@ -504,6 +531,8 @@ hipError_t launch_publish_select(const MlpSelect& m, Ctrl* ctrl, Ctrl* host_dst,
 // instead of once per level.  Each level appends to q[(cur + 1) % 3] and
 // clears the counters of q[(cur + 2) % 3], which nothing reads during it.
 constexpr int kDlMaxN = 4096;        // frontier vertices staged in LDS per level
+constexpr int kDpMaxN = 1 << 16;     // frontier vertices of a k_dpush level (graphs without long rows)
+constexpr int kDpMaxDegree = 64;
 constexpr int kDlMaxLevels = 64;     // levels per block (log capacity)
 constexpr uint32_t kDlMaxRefill = 1u << 16;  // SSSP far-pile entries a block may split itself
 struct DlArgs {
@@ -521,8 +550,9 @@ struct DlArgs {
   Ctrl* ctrl;
   int32_t edges_vs_all = 0;   // 1: push -> pull when m_f > E * do_a (batched BFS's rule)
 };
+// mf: edges of the first frontier (k_dpush levels only)
 hipError_t launch_dl_begin(Ctrl* ctrl, int cur, int64_t vm, int64_t vn, uint32_t pq_T,
-                           int32_t pq_epoch, int32_t pq_fc, hipStream_t st);
+                           int32_t pq_epoch, int32_t pq_fc, hipStream_t st, int64_t mf = 0);
 hipError_t launch_bfs_dstep(const DlArgs& a, uint32_t* bm, int p, int32_t* depth, int32_t* parent,
                             const int32_t* perm, int32_t next_depth, int n_blocks, hipStream_t st);
 hipError_t launch_sssp_dstep(const DlArgs& a, const uint32_t* W, unsigned long long* keys,

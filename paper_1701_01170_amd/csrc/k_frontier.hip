@@ -298,12 +298,13 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, int6
 // block counters, the visited counts before that frontier and the priority
 // queue state of its first step.
 __global__ void k_dl_begin(Ctrl* __restrict__ ctrl, int cur, int64_t vm, int64_t vn,
-                           uint32_t pq_T, int32_t pq_epoch, int32_t pq_fc) {
+                           uint32_t pq_T, int32_t pq_epoch, int32_t pq_fc, int64_t mf) {
   ctrl->dl_levels = 0;
   ctrl->dl_stop = 0;
   ctrl->q_count[(cur + 1) % 3] = 0;
   ctrl->dl_vm[0] = vm;
   ctrl->dl_vn[0] = vn;
+  ctrl->dl_mf[0] = mf;
   ctrl->pq_T[0] = pq_T;
   ctrl->pq_epoch[0] = pq_epoch;
   ctrl->pq_fc[0] = pq_fc;
@@ -355,8 +356,8 @@ hipError_t launch_frontier_offsets(const int32_t* frontier, int64_t n_f, const i
 }
 
 hipError_t launch_dl_begin(Ctrl* ctrl, int cur, int64_t vm, int64_t vn, uint32_t pq_T,
-                           int32_t pq_epoch, int32_t pq_fc, hipStream_t st) {
-  k_dl_begin<<<1, 1, 0, st>>>(ctrl, cur, vm, vn, pq_T, pq_epoch, pq_fc);
+                           int32_t pq_epoch, int32_t pq_fc, hipStream_t st, int64_t mf) {
+  k_dl_begin<<<1, 1, 0, st>>>(ctrl, cur, vm, vn, pq_T, pq_epoch, pq_fc, mf);
   return hipGetLastError();
 }
 
