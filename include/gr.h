@@ -125,14 +125,16 @@ typedef struct gr_opts {
   uint32_t struct_size;      /* sizeof(gr_opts); set by gr_opts_default */
   int32_t policy;            /* gr_policy */
   int32_t fixed_action;      /* gr_action for GR_POLICY_FIXED */
-  int32_t lb_light_threshold;/* PUSH_LB uses input-frontier balance below this frontier size (paper: 4096) */
+  int32_t lb_light_threshold;/* PUSH_LB uses input-frontier balance below this frontier size (paper: 4096),
+                                unless a slice of it would hold thousands of edges */
   uint64_t policy_seed;      /* seed for GR_POLICY_RANDOM */
   float do_a;                /* push -> pull when m_f > m_u * do_a (Sec. 5.1, direction switch) */
   float do_b;                /* pull -> push when m_f < m_u * do_b */
   float lb_min_avg_degree;   /* LB when average degree >= this, else TWC (paper: 5) */
   int32_t max_iterations;    /* stop after this many iterations (<= 0: unlimited) */
-  int32_t lb_chunk;          /* edges per workgroup in output-balanced LB: 0 (default 8192), 512, 1024,
-                                2048, 4096, 8192, 16384 */
+  int32_t lb_chunk;          /* edges per workgroup in output-balanced LB: 512, 1024, 2048, 4096,
+                                8192, 16384, or 0 (default): by the frontier's edges, up to 8192,
+                                in BFS, 1024 in SSSP and BC */
   int32_t trace_capacity;    /* records available in trace */
   gr_level_trace* trace;     /* host array, nullable: per-iteration records */
   int32_t trace_count;       /* out: records written (may exceed capacity; extra are dropped) */

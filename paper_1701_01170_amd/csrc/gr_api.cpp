@@ -201,12 +201,44 @@ gr_status read_ctrl(gr_ctx* ctx, Ctrl* dev, hipStream_t st, const StatsSum& stat
   return GR_OK;
 }
 
-constexpr int kDefaultChunk = 8192;
+// Edges per workgroup of output-balanced LB where the caller leaves it to the
+// library (lb_chunk = 0).  BFS expansions gain from long chunks (32 edges in
+// flight per lane) as long as enough workgroups remain to fill the chip: the
+// largest size that still gives kLbGroups of them, four per CU.  The passes whose edges each gather an 8-byte value (SSSP, BC) run best with 1024
+// edges at every size (with 8192 a frontier of 197 K edges is 25 workgroups on
+// 256 CUs: directed uniform graph of 300 K vertices, SSSP 1.81 ms against
+// 1.18 ms), and their degree scan is queued before the host knows the
+// frontier's size.
+constexpr int kBfsChunk = 8192;
+constexpr int kGatherChunk = 1024;
+constexpr int kMinChunk = 512;
+constexpr int64_t kLbGroups = 1024;
+int bfs_chunk(const gr_opts& o, int64_t m_f) {
+  if (o.lb_chunk > 0) return o.lb_chunk;
+  int c = kBfsChunk;
+  while (c > kMinChunk && m_f < c * kLbGroups) c /= 2;
+  return c;
+}
+
+// How a push level expands its frontier: 0 = TWC, 1 = LB_LIGHT (equal slices of
+// the frontier), 2 = LB (equal chunks of its edges).  Light slices save the
+// degree scan, but a slice that holds a hub's row leaves its workgroup to work
+// through it alone while the others end: they are used only while no slice can
+// hold more than kLightMaxEdges edges by much (R-MAT 22 with the default knobs,
+// whose second frontier is some 100 hubs with 0.5 M edges, one light slice: BFS
+// 6.6 ms, SSSP 13.2 ms; as LB 0.58 and 2.2 ms).
+constexpr int64_t kLightMaxEdges = 4096;
+int push_mode(int action, const gr_opts& o, int block, int64_t n_f, int64_t m_f, int64_t max_deg) {
+  if (action == GR_PUSH_TWC) return 0;
+  if (n_f >= o.lb_light_threshold) return 2;
+  const int64_t slices = (n_f + block - 1) / block;
+  return max_deg <= kLightMaxEdges && m_f <= slices * kLightMaxEdges ? 1 : 2;
+}
 
 // The push kernels' launch shape from the options (validated by check_opts).
 AdvCfg adv_cfg(const gr_opts& o) {
   AdvCfg c;
-  c.chunk = o.lb_chunk > 0 ? o.lb_chunk : kDefaultChunk;
+  c.chunk = o.lb_chunk > 0 ? o.lb_chunk : kGatherChunk;
   c.block = o.adv_block > 0 ? o.adv_block : 256;
   c.twc_wave_min = o.twc_wave_min > 0 ? o.twc_wave_min : -1;
   c.twc_block_min = o.twc_block_min > 0 ? o.twc_block_min : -1;
@@ -883,8 +915,7 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
                   Arena& ar, bool internal_ids = false) {
   const int64_t V = g->V, E = g->E, NW = words_for(V);
   const bool pull_ok = (g->flags & GR_SYMMETRIC) != 0;
-  const AdvCfg adv = adv_cfg(opts);
-  const int chunk = adv.chunk;
+  AdvCfg adv = adv_cfg(opts);
   const bool tracing = opts_in && opts_in->trace;
 
   const bool idem = bfs_idem_on(opts, pull_ok);
@@ -1044,10 +1075,11 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
     const int next_depth = level + 1;
     int kernel = 0;
     if (action == GR_PUSH_LB || action == GR_PUSH_TWC) {
-      const int mode = action == GR_PUSH_TWC ? 0 : (n_f < opts.lb_light_threshold ? 1 : 2);
+      const int mode = push_mode(action, opts, adv.block, n_f, m_f, max_deg);
+      adv.chunk = bfs_chunk(opts, m_f);
       if (mode == 2)
         GR_HIP(launch_frontier_offsets(q[cur], n_f, g->R, bsums, offsets, rstart,
-                                       chunks, chunk, st));
+                                       chunks, adv.chunk, st));
       // canonical parents by an atomic minimum in the push (about one atomic
       // per frontier edge) or by the fix-up scan of the new vertices, which
       // reads each sorted list up to its first frontier neighbour: about E / m_f
@@ -1441,7 +1473,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
       pq.epoch += 1;
       pq.fc = (pq.fc + 1) % 3;
     } else {
-      const int mode = action == GR_PUSH_TWC ? 0 : (n_f < opts.lb_light_threshold ? 1 : 2);
+      const int mode = push_mode(action, opts, adv.block, n_f, m_f, max_deg);
       kernel = mode;
       if (mode == 2 && !offsets_ready)
         GR_HIP(launch_frontier_offsets(q[cur], n_f, g->R, bsums, offsets, rstart,
@@ -1535,8 +1567,7 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t V = g->V, E = g->E;
   const int G = stats_grid();
-  const AdvCfg adv = adv_cfg(opts);
-  const int chunk = adv.chunk;
+  AdvCfg adv = adv_cfg(opts);
   const bool use_lb = (double)E / (double)V >= (double)opts.lb_min_avg_degree;
   using u64 = unsigned long long;
 
@@ -1724,11 +1755,12 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
                               rstart, ctrl->ms_big, st));
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k1, st));
       } else {
-        const int mode = action == GR_PUSH_TWC ? 0 : (n_a < opts.lb_light_threshold ? 1 : 2);
+        const int mode = push_mode(action, opts, adv.block, n_a, m_a, hc->max_deg[sp]);
+        adv.chunk = bfs_chunk(opts, m_a);
         kernel = mode;
         if (mode == 2)
           GR_HIP(launch_frontier_offsets(q[cur], n_a, g->R, bsums, offsets, rstart,
-                                         chunks, chunk, st));
+                                         chunks, adv.chunk, st));
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k0, st));
         GR_HIP(launch_ms_push(mode, q[cur], offsets, rstart, chunks, n_a, m_a, g->R, g->C,
                               front[fc], visit, next, out, V, g->perm, q[(cur + 1) % 3],

@@ -193,7 +193,7 @@ gr_status pool_get(gr_ctx* ctx, Slot s, size_t bytes, void** out);
 // Launch shape of the push-advance kernels (tuning knobs: the results never
 // depend on them).
 struct AdvCfg {
-  int chunk = 8192;         // LB: edges per workgroup (512 .. 16384, powers of two)
+  int chunk = 1024;         // LB: edges per workgroup (512 .. 16384, powers of two)
   int block = 256;          // workgroup size: 128, 256 or 512
   int twc_wave_min = -1;    // TWC: lists longer than this go to a wavefront (< 0: 64)
   int twc_block_min = -1;   // TWC: lists longer than this go to the workgroup (< 0: block)
