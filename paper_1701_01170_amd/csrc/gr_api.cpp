@@ -2096,12 +2096,10 @@ extern "C" gr_status gr_bc(gr_ctx* ctx, const gr_graph* g, const int32_t* source
       if (!push)
         return launch_bc_pull(dependency, f, o, r, cm, hn[x], (int64_t)hm[x], tab[L + x], chunk,
                               g->C, depth, want, sig, acc, st);
-      const int mode = lb ? 2 : 0;
-      if (dependency)
-        return launch_bc_dependency(mode, f, o, r, cm, hn[x], (int64_t)hm[x], tab[L + x], g->R,
-                                    g->C, depth, sig, acc, want, adv, st);
-      return launch_bc_sigma(mode, f, o, r, cm, hn[x], (int64_t)hm[x], tab[L + x], g->R, g->C,
-                             depth, sig, want, adv, st);
+      if (lb)
+        return launch_bc_push(dependency, f, o, r, cm, hn[x], (int64_t)hm[x], tab[L + x], chunk,
+                              g->C, depth, want, sig, acc, ctx->cu_count, st);
+      return launch_bc_push_twc(dependency, f, hn[x], g->R, g->C, depth, want, sig, acc, adv, st);
     };
     // forward: sigma of level d + 1 from level d, pushed by level d or
     // gathered by level d + 1

@@ -347,18 +347,18 @@ hipError_t launch_bc_levels(const int32_t* depth, const int32_t* R, int64_t V, i
                             double* sigma, double* acc, hipStream_t st);
 hipError_t launch_bc_scatter(const int32_t* depth, int64_t V, int32_t n_levels, uint32_t* cursor,
                              int32_t* levels, hipStream_t st);
-// push form of either pass over one level (mode 0 = TWC, 2 = LB; the level's
-// edges at positions e_base .. of `offsets`)
-hipError_t launch_bc_sigma(int mode, const int32_t* frontier, const int32_t* offsets,
-                           const int32_t* rstart, const int32_t* chunk_start, int64_t n_f,
-                           int64_t m_f, int64_t e_base, const int32_t* R, const int32_t* C,
-                           const int32_t* depth, double* sigma, int32_t next_depth,
-                           const AdvCfg& cfg, hipStream_t st);
-hipError_t launch_bc_dependency(int mode, const int32_t* frontier, const int32_t* offsets,
-                                const int32_t* rstart, const int32_t* chunk_start, int64_t n_f,
-                                int64_t m_f, int64_t e_base, const int32_t* R, const int32_t* C,
-                                const int32_t* depth, const double* sigma, double* acc,
-                                int32_t prev_depth, const AdvCfg& cfg, hipStream_t st);
+// push form of either pass over one level's rows (dependency: into acc of the
+// vertices at depth `want`; otherwise into their sigma): over LB chunks (the
+// level's edges at positions e_base .. of `offsets`), or by TWC
+hipError_t launch_bc_push(bool dependency, const int32_t* frontier, const int32_t* offsets,
+                          const int32_t* rstart, const int32_t* chunk_start, int64_t n_f,
+                          int64_t m_f, int64_t e_base, int chunk, const int32_t* C,
+                          const int32_t* depth, int32_t want, double* sigma, double* acc,
+                          int cu_count, hipStream_t st);
+hipError_t launch_bc_push_twc(bool dependency, const int32_t* frontier, int64_t n_f,
+                              const int32_t* R, const int32_t* C, const int32_t* depth,
+                              int32_t want, double* sigma, double* acc, const AdvCfg& cfg,
+                              hipStream_t st);
 // per-level chunk maps of both passes for every level at once (offsets:
 // the degree scan over all n_r vertices in level order; tab: per level its
 // first vertex index, first edge position and first chunk, 3 * n_levels)

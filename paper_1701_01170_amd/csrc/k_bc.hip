@@ -62,6 +62,10 @@ struct BcDependency {
 
 constexpr int kBcBlock = 256;
 constexpr int kBcItems = 8;            // vertices per thread per tile
+constexpr int kBcPushBlock = 512;
+constexpr int kBcSlotsLog = 12;
+constexpr int kBcSlots = 1 << kBcSlotsLog;
+constexpr int kBcPushGroups = 2;       // workgroups per CU of the push form
 constexpr int kBcLdsLevels = 4096;     // levels counted in LDS (more: global atomics)
 
 // Vertices per level and their degree sums; sigma / acc initialised
@@ -272,6 +276,106 @@ __global__ __launch_bounds__(kBcBlock) void k_bc_pull_lb(
   }
 }
 
+// Push form of a pass over LB chunks: every edge (w, v) of the level's rows with
+// depth(v) == want adds pay(w) to out(v).  The fp64 atomics bound it: spread
+// over many addresses they run at 20-25 G/s, and those on one address queue one
+// behind another, while most edges of a deep level end at few hubs.  So each
+// workgroup adds up its share of the hubs in LDS first: a direct-mapped table of
+// kBcSlots vertices, a slot taken by the first vertex that hashes to it and kept (a
+// hub comes early), the other vertices of a taken slot going to memory directly.
+// Workgroups stay for many chunks (kBcPushGroups per CU, consecutive chunks each),
+// and add their table to memory once at the end.  R-MAT 22, 17 M edges pushed into
+// 0.49 M vertices: 1.93 -> 0.88 ms.  (2048 slots and four workgroups of 256 per CU:
+// 1.08 ms; 8192 slots and one of 512: the same as here; a copy of the sums per XCD,
+// so that no line travels between their caches: 0.84 ms and 10 us more for each
+// small level.)
+template <class Pay, int EPT, int NB>
+__global__ __launch_bounds__(kBcPushBlock) void k_bc_push_lb(
+    const int32_t* __restrict__ frontier, const int32_t* __restrict__ offsets,
+    const int32_t* __restrict__ rstart, const int32_t* __restrict__ chunk_start, int32_t n_f,
+    int32_t m_f, int64_t e_base, const int32_t* __restrict__ C, const int32_t* __restrict__ depth,
+    int32_t want, Pay pay, double* __restrict__ out) {
+  constexpr int BLOCK = kBcPushBlock;
+  constexpr int BATCH = BLOCK * EPT;
+  constexpr int N = BATCH * NB;
+  constexpr int SPT = N / BLOCK;
+  constexpr int CAP = lb_cap(N);
+  __shared__ double s_sum[kBcSlots];
+  __shared__ int32_t s_tag[kBcSlots];
+  __shared__ double s_pay[CAP];
+  __shared__ uint16_t s_seg[N];
+  __shared__ int32_t s_off[CAP + 1];
+  __shared__ int32_t s_rb[CAP];
+  __shared__ int32_t s_tmp[BLOCK / kWave + 1];
+  for (int i = threadIdx.x; i < kBcSlots; i += BLOCK) {
+    s_sum[i] = 0.0;
+    s_tag[i] = -1;
+  }
+  const int nchunks = (int)(((int64_t)m_f + N - 1) / N);
+  const int per = (nchunks + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int c0 = (int)blockIdx.x * per, c1 = c0 + per < nchunks ? c0 + per : nchunks;
+  for (int c = c0; c < c1; ++c) {
+    const int64_t e0 = e_base + (int64_t)c * N;
+    const int64_t e1 = e0 + N < e_base + m_f ? e0 + N : e_base + m_f;
+    const int sb = chunk_start[c];
+    const int se = c + 1 < nchunks ? chunk_start[c + 1] : n_f - 1;
+    for (int pb = sb; pb <= se; pb += CAP) {
+      const int cnt = (se - pb + 1) < CAP ? (se - pb + 1) : CAP;
+      for (int i = threadIdx.x; i < cnt; i += BLOCK) {
+        const int s = pb + i;
+        s_off[i] = offsets[s];
+        s_rb[i] = rstart[s];
+        s_pay[i] = pay(frontier[s]);
+      }
+      if (threadIdx.x == 0) s_off[cnt] = offsets[pb + cnt];
+      for (int j = threadIdx.x; j < N; j += BLOCK) s_seg[j] = 0;
+      __syncthreads();
+      const int64_t lo = e0 > (int64_t)s_off[0] ? e0 : (int64_t)s_off[0];
+      const int64_t hi = e1 < (int64_t)s_off[cnt] ? e1 : (int64_t)s_off[cnt];
+      for (int k = 1 + threadIdx.x; k < cnt; k += BLOCK) {
+        const int64_t pos = (int64_t)s_off[k] - lo;
+        if (pos < hi - lo && s_off[k + 1] > s_off[k]) s_seg[pos] = (uint16_t)k;
+      }
+      __syncthreads();
+      lb_seg_maxscan<SPT, BLOCK>(s_seg, s_tmp);
+      __syncthreads();
+      for (int b = 0; b < NB; ++b) {
+        if (lo + (int64_t)b * BATCH >= hi) break;
+        int32_t v[EPT];
+        double x[EPT];
+#pragma unroll
+        for (int r = 0; r < EPT; ++r) {
+          const int j = b * BATCH + r * BLOCK + threadIdx.x;
+          const int64_t e = lo + j;
+          const bool ok = e < hi;
+          const int k = ok ? (int)s_seg[j] : 0;
+          v[r] = ok ? C[s_rb[k] + (int32_t)(e - s_off[k])] : -1;
+          x[r] = s_pay[k];
+        }
+#pragma unroll
+        for (int r = 0; r < EPT; ++r)
+          if (v[r] >= 0 && depth[v[r]] != want) v[r] = -1;
+#pragma unroll
+        for (int r = 0; r < EPT; ++r) {
+          if (v[r] < 0) continue;
+          const uint32_t slot = ((uint32_t)v[r] * 2654435761u) >> (32 - kBcSlotsLog);
+          int32_t t = s_tag[slot];
+          if (t < 0) {
+            t = atomicCAS(&s_tag[slot], -1, v[r]);
+            if (t < 0) t = v[r];
+          }
+          if (t == v[r]) unsafeAtomicAdd(&s_sum[slot], x[r]);
+          else unsafeAtomicAdd(&out[v[r]], x[r]);
+        }
+      }
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kBcSlots; i += BLOCK)
+    if (s_tag[i] >= 0) unsafeAtomicAdd(&out[s_tag[i]], s_sum[i]);
+}
+
 // The chunk -> first-row maps of the pull passes for every level in one
 // launch.  The n_r reached vertices are stored level after level (`levels`)
 // and `offsets` is one exclusive scan of their degrees over all of them, so
@@ -328,24 +432,15 @@ hipError_t launch_bc_scatter(const int32_t* depth, int64_t V, int32_t n_levels, 
   return hipGetLastError();
 }
 
-hipError_t launch_bc_sigma(int mode, const int32_t* frontier, const int32_t* offsets,
-                           const int32_t* rstart, const int32_t* chunk_start, int64_t n_f,
-                           int64_t m_f, int64_t e_base, const int32_t* R, const int32_t* C,
-                           const int32_t* depth, double* sigma, int32_t next_depth,
-                           const AdvCfg& cfg, hipStream_t st) {
-  const BcSigma f{depth, sigma, next_depth};
-  return push_dispatch(mode, frontier, offsets, rstart, chunk_start, n_f, m_f, R, C, f, nullptr,
-                       nullptr, cfg, st, e_base);
-}
-
-hipError_t launch_bc_dependency(int mode, const int32_t* frontier, const int32_t* offsets,
-                                const int32_t* rstart, const int32_t* chunk_start, int64_t n_f,
-                                int64_t m_f, int64_t e_base, const int32_t* R, const int32_t* C,
-                                const int32_t* depth, const double* sigma, double* acc,
-                                int32_t prev_depth, const AdvCfg& cfg, hipStream_t st) {
-  const BcDependency f{depth, sigma, acc, prev_depth};
-  return push_dispatch(mode, frontier, offsets, rstart, chunk_start, n_f, m_f, R, C, f, nullptr,
-                       nullptr, cfg, st, e_base);
+hipError_t launch_bc_push_twc(bool dependency, const int32_t* frontier, int64_t n_f,
+                              const int32_t* R, const int32_t* C, const int32_t* depth,
+                              int32_t want, double* sigma, double* acc, const AdvCfg& cfg,
+                              hipStream_t st) {
+  if (dependency)
+    return push_dispatch(0, frontier, nullptr, nullptr, nullptr, n_f, 0, R, C,
+                         BcDependency{depth, sigma, acc, want}, nullptr, nullptr, cfg, st);
+  return push_dispatch(0, frontier, nullptr, nullptr, nullptr, n_f, 0, R, C,
+                       BcSigma{depth, sigma, want}, nullptr, nullptr, cfg, st);
 }
 
 hipError_t launch_bc_chunk_map(const int32_t* levels, const int32_t* depth, int64_t n_r,
@@ -354,6 +449,42 @@ hipError_t launch_bc_chunk_map(const int32_t* levels, const int32_t* depth, int6
   if (n_r <= 0) return hipSuccess;
   k_bc_chunk_map<<<blocks_of(n_r, kBcBlock), kBcBlock, 0, st>>>(levels, depth, n_r, offsets, tab,
                                                                 n_levels, chunk, chunk_map);
+  return hipGetLastError();
+}
+
+hipError_t launch_bc_push(bool dependency, const int32_t* frontier, const int32_t* offsets,
+                          const int32_t* rstart, const int32_t* chunk_start, int64_t n_f,
+                          int64_t m_f, int64_t e_base, int chunk, const int32_t* C,
+                          const int32_t* depth, int32_t want, double* sigma, double* acc,
+                          int cu_count, hipStream_t st) {
+  if (n_f <= 0 || m_f <= 0) return hipSuccess;
+  unsigned g = blocks_of(m_f, chunk);
+  const unsigned most = (unsigned)(cu_count * kBcPushGroups);
+  if (g > most) g = most;
+#define GR_BC_PUSH(CH)                                                                          \
+  case CH: {                                                                                    \
+    constexpr int ept = (CH / kBcPushBlock) < 8 ? (CH / kBcPushBlock) : 8;                      \
+    constexpr int nb = CH / (kBcPushBlock * ept);                                               \
+    if (dependency)                                                                             \
+      k_bc_push_lb<BcDependencyVal, ept, nb><<<g, kBcPushBlock, 0, st>>>(                       \
+          frontier, offsets, rstart, chunk_start, (int32_t)n_f, (int32_t)m_f, e_base, C, depth, \
+          want, BcDependencyVal{sigma, acc}, acc);                                              \
+    else                                                                                        \
+      k_bc_push_lb<BcSigmaVal, ept, nb><<<g, kBcPushBlock, 0, st>>>(                            \
+          frontier, offsets, rstart, chunk_start, (int32_t)n_f, (int32_t)m_f, e_base, C, depth, \
+          want, BcSigmaVal{sigma}, sigma);                                                      \
+    break;                                                                                      \
+  }
+  switch (chunk) {
+    GR_BC_PUSH(512)
+    GR_BC_PUSH(1024)
+    GR_BC_PUSH(2048)
+    GR_BC_PUSH(4096)
+    GR_BC_PUSH(16384)
+    default:
+      GR_BC_PUSH(8192)
+  }
+#undef GR_BC_PUSH
   return hipGetLastError();
 }
 
