@@ -701,7 +701,12 @@ gr_status record_trace(gr_ctx* ctx, gr_opts* opts, const LevelFeatures& lf, int 
 }
 
 // ---- iteration control: device-predicated blocks of push levels ----------
-constexpr int kDlFirstLen = 4;              // levels in the first block (then adapted per block)
+// A block of gr_bfs / gr_sssp: k_team, then pairs of k_dstep and k_team (so many in
+// the first block, then adapted: a block that ends with levels left doubles the
+// next one, one that stops halves it).  gr_bfs_multi: so many levels.
+constexpr int kDlFirstPairs = 1, kDlMaxPairs = 16;
+static_assert(2 * kDlMaxPairs + 1 <= kTeamWords, "a team word per kernel of a block");
+constexpr int kDlFirstLen = 4;
 constexpr int64_t kDlDefaultMaxEdges = 1 << 18;
 constexpr int kTraceKernelDstep = 6;
 constexpr int kTraceKernelRefill = 7;
@@ -726,14 +731,20 @@ constexpr int64_t kSsspMirrorDivisor = 8;
 struct DlPlan {
   bool on = false;
   int64_t max_m = 0;
-  double do_a = -1.0;   // device push -> pull test (< 0: none)
-
-  int len = kDlFirstLen;
+  int len = kDlFirstPairs;  // pairs in the next block
   int blocks = 256;
   int64_t* log = nullptr;
   bool graph = false;   // record each block as a hipGraph
+  int log_w = -1;       // DlArgs::log_w of the graph
 };
 constexpr int kGraphKeyBfs = 0, kGraphKeySssp = 1, kGraphKeySsspPq = 2;
+
+// The most levels of a block that starts at level `level` (tracing: what its log
+// holds).
+int dl_max_steps(bool tracing, const gr_opts& o, int level) {
+  const int n = tracing ? kDlMaxLevels : kBlockMaxSteps;
+  return o.max_iterations > 0 ? std::min(n, o.max_iterations - level) : n;
+}
 
 // hipGraph iteration control.  While a block of device-predicated levels is
 // enqueued, its launches go to the context's capture stream (nothing runs
@@ -795,17 +806,17 @@ gr_status block_capture_launch(gr_ctx* ctx, BlockCapture* bc, int key, hipStream
   return GR_OK;
 }
 
-gr_status dl_plan(gr_ctx* ctx, Arena& ar, const gr_opts& o, bool pull_ok, bool learned,
+gr_status dl_plan(gr_ctx* ctx, Arena& ar, const gr_graph* g, const gr_opts& o, bool learned,
                   bool tracing, DlPlan* d) {
   const bool heuristic = o.policy == GR_POLICY_HEURISTIC ||
                          (o.policy == GR_POLICY_LEARNED && !learned);
   d->on = o.device_max_edges >= 0 && (heuristic || learned || o.policy == GR_POLICY_FIXED);
   d->max_m = o.device_max_edges > 0 ? o.device_max_edges : kDlDefaultMaxEdges;
-  d->do_a = (heuristic || learned) && pull_ok ? (double)o.do_a : -1.0;
-
-  d->len = kDlFirstLen;
+  d->len = kDlFirstPairs;
   d->blocks = ctx->cu_count > 0 ? ctx->cu_count : 256;
   d->log = nullptr;
+  // (the block log's largest degrees come from the staged form)
+  d->log_w = tracing || g->max_degree > 8 ? -1 : g->max_degree > 4 ? 3 : 2;
   d->graph = o.graph_blocks == 1 && !tracing && !ar.fixed();
   if (d->on && tracing) GR_TRY(ar.get(S_DLOG, 3 * kDlMaxLevels, &d->log));
   return GR_OK;
@@ -980,7 +991,7 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
   int level = 0;
   gr_run_stats rs{};
   DlPlan dl;
-  GR_TRY(dl_plan(ctx, ar, opts, pull_ok, learned, tracing, &dl));
+  GR_TRY(dl_plan(ctx, ar, g, opts, learned, tracing, &dl));
 
   while (n_f > 0 && (opts.max_iterations <= 0 || level < opts.max_iterations)) {
     lf.level = level;
@@ -997,25 +1008,24 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
     if (dl_fits && (action == GR_PUSH_LB || action == GR_PUSH_TWC)) {
       // A block of device-predicated push levels (atomic parents, no merge
       // pass); its first level is the one just decided on the host.
-      int kmax = dl.len;
-      if (opts.max_iterations > 0) kmax = (int)std::min<int64_t>(kmax, opts.max_iterations - level);
+      const int max_steps = dl_max_steps(tracing, opts, level);
       const int64_t vm0 = visited_m - m_f, vn0 = visited_n - n_f;
-      // the network pushing where the heuristic would pull: the block keeps
-      // pushing (its device-side direction test would stop it at once)
-      const double blk_do_a = sel.last_heuristic >= GR_PULL_TWC ? -1.0 : dl.do_a;
       BlockCapture capture;
       hipStream_t es = st;
       if (dl.graph) GR_TRY(block_capture_begin(ctx, &capture, &es));
-      GR_HIP(launch_dl_begin(ctrl, cur, vm0, vn0, 0u, 0, 0, es));
+      GR_HIP(launch_dl_begin(ctrl, cur, vm0, vn0, 0u, 0, 0, es, 0, bsums));
       if (tracing) GR_HIP(hipEventRecord(ctx->ev_a, st));
-      for (int i = 0; i < kmax; ++i) {
-        const int qc = (cur + i) % 3;
-        const DlArgs da{g->R, g->C, q[qc], q[(qc + 1) % 3], qc, i, kDlMaxN, dl.max_m, E, blk_do_a,
-                        V, dl.log, ctrl};
-        GR_HIP(launch_bfs_dstep(da, bm, p ^ (i & 1), depth, parent, perm, level + i + 1, dl.blocks,
-                                es));
+      for (int i = 0; i <= 2 * dl.len; ++i) {
+        DlArgs da{g->R, g->C, nullptr, nullptr, 0, 0, kDlMaxN, dl.max_m, E, -1.0, V, dl.log, ctrl};
+        da.qs = Queues3{{qA, qB, qC}};
+        da.cur0 = cur;
+        da.seq = i;
+        da.max_steps = max_steps;
+        da.team = bsums;  // (the statistics are through with them)
+        da.log_w = dl.log_w;
+        GR_HIP(launch_bfs_dstep(da, bm, p, depth, parent, perm, level + 1, !(i & 1), dl.blocks, es));
       }
-      if (dl.graph) GR_TRY(block_capture_launch(ctx, &capture, (kGraphKeyBfs << 8) | kmax, st));
+      if (dl.graph) GR_TRY(block_capture_launch(ctx, &capture, (kGraphKeyBfs << 8) | dl.len, st));
       if (tracing) GR_HIP(hipEventRecord(ctx->ev_b, st));
       // statistics of the frontier the block leaves (found on the device),
       // then a single read-back; with k == 0 levels run the frontier is
@@ -1027,17 +1037,17 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
       msel.after_block = 1;
       // while tracing, the publication also copies the block's level log
       const PublishExtra lgx{reinterpret_cast<const uint32_t*>(dl.log),
-                             reinterpret_cast<uint32_t*>(ctx->host_dlog_dev), 6 * kmax};
+                             reinterpret_cast<uint32_t*>(ctx->host_dlog_dev), 6 * kDlMaxLevels};
       GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr, nullptr,
                        tracing ? &lgx : nullptr));
       const int k = hc->dl_levels;
+      if (hc->dl_fail) return fail(GR_EHIP, "a device-side wait of a block of levels ran out");
       if (k > 0) {
         const int64_t* lg = ctx->host_dlog;  // the block's level log (host copy)
         float block_ms = 0.f;
         if (tracing) GR_TRY(elapsed_ms(ctx->ev_a, ctx->ev_b, &block_ms));
-        // full blocks double the next one; blocks that stop early halve it
-        if (k == kmax) dl.len = std::min(2 * dl.len, kDlMaxLevels);
-        else if (2 * k < kmax) dl.len = std::max(dl.len / 2, kDlFirstLen);
+        dl.len = hc->dl_stop ? std::max(dl.len / 2, kDlFirstPairs)
+                             : std::min(2 * dl.len, kDlMaxPairs);
         rs.action_count[action] += k;
         inspected_push += hc->dl_vm[k & 1] - vm0;
         visited_n = hc->dl_vn[k & 1];
@@ -1355,7 +1365,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
   DlPlan dl;
   Arena ar;
   ar.ctx = ctx;
-  GR_TRY(dl_plan(ctx, ar, opts, /*pull_ok=*/false, learned, tracing, &dl));
+  GR_TRY(dl_plan(ctx, ar, g, opts, learned, tracing, &dl));
   // after a step that produced the frontier in q[cur]: statistics, selector, read-back
   // with load-balanced advance likely (average degree), the degree scan of
   // each new frontier is queued ahead of the read-back (offsets_ready)
@@ -1392,23 +1402,29 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
       // A block of device-predicated relaxation rounds (Alg. 1 iterations;
       // with the priority queue also its refill steps).
       offsets_ready = false;  // the block leaves a frontier the scan has not seen
-      int kmax = dl.len;
-      if (opts.max_iterations > 0) kmax = std::min(kmax, opts.max_iterations - it);
+      const int max_steps = dl_max_steps(tracing, opts, it);
       BlockCapture capture;
       hipStream_t es = st;
       if (dl.graph) GR_TRY(block_capture_begin(ctx, &capture, &es));
-      GR_HIP(launch_dl_begin(ctrl, cur, 0, 0, pq.T, pq.epoch, pq.fc, es));
+      GR_HIP(launch_dl_begin(ctrl, cur, 0, 0, pq.T, pq.epoch, pq.fc, es, 0, bsums));
       if (tracing) GR_HIP(hipEventRecord(ctx->ev_a, st));
-      for (int i = 0; i < kmax; ++i) {
-        const int qc = (cur + i) % 3;
-        const DlArgs da{g->R, g->C, q[qc], q[(qc + 1) % 3], qc, i, kDlMaxN, dl.max_m, E, -1.0,
-                        V, dl.log, ctrl};
-        if (use_pq) GR_HIP(launch_sssp_pq_dstep(da, g->W, keys, tags, it + i + 1, pq, dl.blocks, es));
-        else GR_HIP(launch_sssp_dstep(da, g->W, keys, tags, perm, it + i + 1, dl.blocks, es));
+      for (int i = 0; i <= 2 * dl.len; ++i) {
+        DlArgs da{g->R, g->C, nullptr, nullptr, 0, 0, kDlMaxN, dl.max_m, E, -1.0, V, dl.log, ctrl};
+        da.qs = Queues3{{qA, qB, qC}};
+        da.cur0 = cur;
+        da.seq = i;
+        da.max_steps = max_steps;
+        da.team = bsums;  // (the statistics and the degree scan are through with them)
+        da.log_w = dl.log_w;
+        const bool team = !(i & 1);
+        if (use_pq)
+          GR_HIP(launch_sssp_pq_dstep(da, g->W, keys, tags, it + 1, pq, team, dl.blocks, es));
+        else
+          GR_HIP(launch_sssp_dstep(da, g->W, keys, tags, perm, it + 1, team, dl.blocks, es));
       }
       if (dl.graph)
         GR_TRY(block_capture_launch(ctx, &capture,
-                                    ((use_pq ? kGraphKeySsspPq : kGraphKeySssp) << 8) | kmax, st));
+                                    ((use_pq ? kGraphKeySsspPq : kGraphKeySssp) << 8) | dl.len, st));
       if (tracing) GR_HIP(hipEventRecord(ctx->ev_b, st));
       // statistics of the frontier the block leaves, then a single read-back
       // (with k == 0 levels run the statistics just move to the other slot)
@@ -1418,10 +1434,11 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
       msel.sp = sp;
       // while tracing, the publication also copies the block's level log
       const PublishExtra lgx{reinterpret_cast<const uint32_t*>(dl.log),
-                             reinterpret_cast<uint32_t*>(ctx->host_dlog_dev), 6 * kmax};
+                             reinterpret_cast<uint32_t*>(ctx->host_dlog_dev), 6 * kDlMaxLevels};
       GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr, nullptr,
                        tracing ? &lgx : nullptr));
       const int k = hc->dl_levels;
+      if (hc->dl_fail) return fail(GR_EHIP, "a device-side wait of a block of levels ran out");
       if (use_pq) {
         pq.T = hc->pq_T[k & 1];
         pq.epoch = hc->pq_epoch[k & 1];
@@ -1432,9 +1449,8 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
         const int64_t* lg = ctx->host_dlog;  // the block's level log (host copy)
         float block_ms = 0.f;
         if (tracing) GR_TRY(elapsed_ms(ctx->ev_a, ctx->ev_b, &block_ms));
-        // full blocks double the next one; blocks that stop early halve it
-        if (k == kmax) dl.len = std::min(2 * dl.len, kDlMaxLevels);
-        else if (2 * k < kmax) dl.len = std::max(dl.len / 2, kDlFirstLen);
+        dl.len = hc->dl_stop ? std::max(dl.len / 2, kDlFirstPairs)
+                             : std::min(2 * dl.len, kDlMaxPairs);
         rs.action_count[action] += k;
         inspected += hc->dl_vm[k & 1];
         expanded += hc->dl_vn[k & 1];
@@ -1720,6 +1736,9 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
           DlArgs da{g->R, g->C, q[qc], q[(qc + 1) % 3], qc, i, dl_max_n, dl_max_m, E, blk_do_a, V,
                     nullptr, ctrl};
           da.edges_vs_all = 1;
+          da.qs = Queues3{{qA, qB, qC}};
+          da.cur0 = cur;
+          da.seq = i;
           const MsLevel ml{g->R, g->C, front[fi], front[fi ^ 1], visit, next, out,
                            g->perm, V, level + i + 1};
           GR_HIP(launch_ms_dlevel(da, ml, short_rows, dl_blocks, std::min<int64_t>(V, dl_max_m),

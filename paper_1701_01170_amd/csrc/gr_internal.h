@@ -106,7 +106,8 @@ struct Ctrl {
   int32_t pad0;
   uint32_t ul_count[2];     // BFS pull: lengths of the two unvisited lists
   uint32_t ms_big[2];       // batched BFS pull: rows listed for the wavefront / workgroup tier
-  uint32_t pad3[4];
+  int32_t dl_step[2];       // levels of the block that ran, as the block's next kernel reads it
+  uint32_t pad3[2];
   // device-predicated level blocks (iteration control without host round trips)
   int32_t dl_levels;        // levels of the current block that ran
   int32_t dl_stop;          // a level of the block declined to run
@@ -119,7 +120,7 @@ struct Ctrl {
   int32_t pq_epoch[2];      // far-pile generation (dedups far appends)
   int32_t pq_fc[2];         // far pile in use (of three rotating piles)
   uint32_t far_count[3];    // far pile lengths
-  uint32_t pad2;
+  uint32_t dl_fail;         // a team's wait ran out (never on a healthy device)
   // multi-source BFS: (source, vertex) pairs reached so far and the sum of
   // their degrees (the selector's unvisited counts, averaged over sources)
   int64_t ms_pairs;
@@ -531,6 +532,10 @@ hipError_t launch_publish_select(const MlpSelect& m, Ctrl* ctrl, Ctrl* host_dst,
 // instead of once per level.  Each level appends to q[(cur + 1) % 3] and
 // clears the counters of q[(cur + 2) % 3], which nothing reads during it.
 constexpr int kDlMaxN = 4096;        // frontier vertices staged in LDS per level
+constexpr int kTeamMaxM = 1 << 15;   // edges of a k_team level
+constexpr int kTeamMaxStaged = 2048; // vertices of one where every workgroup stages them all
+constexpr int kTeamWords = 40;       // k_team kernels of one block
+constexpr int kBlockMaxSteps = 4096; // levels of one block (bounds the time of one kernel)
 constexpr int kDpMaxN = 1 << 16;     // frontier vertices of a k_dpush level (graphs without long rows)
 constexpr int kDpMaxDegree = 64;
 constexpr int kDlMaxLevels = 64;     // levels per block (log capacity)
@@ -549,15 +554,31 @@ struct DlArgs {
   int64_t* log;               // [kDlMaxLevels][3]
   Ctrl* ctrl;
   int32_t edges_vs_all = 0;   // 1: push -> pull when m_f > E * do_a (batched BFS's rule)
+  // k_dstep and k_team: the queues, the block's first one, this kernel's place in
+  // the block and the block's most levels (q_cur, q_next, cur, step: k_dpush);
+  // k_team: its words [kTeamWords] and the log2 of the edge slots per vertex where no
+  // row is longer (-1: rows of any length)
+  Queues3 qs = {};
+  int32_t cur0 = 0;
+  int32_t seq = 0;
+  int32_t max_steps = 1 << 30;
+  int64_t* team = nullptr;
+  int32_t log_w = -1;
 };
-// mf: edges of the first frontier (k_dpush levels only)
+// mf: edges of the first frontier (k_dpush levels only); team: the k_team words,
+// cleared (nullable)
 hipError_t launch_dl_begin(Ctrl* ctrl, int cur, int64_t vm, int64_t vn, uint32_t pq_T,
-                           int32_t pq_epoch, int32_t pq_fc, hipStream_t st, int64_t mf = 0);
+                           int32_t pq_epoch, int32_t pq_fc, hipStream_t st, int64_t mf = 0,
+                           int64_t* team = nullptr);
+// A kernel of a block on n_blocks workgroups: one level (k_dstep), or with `team`
+// small levels on those of one XCD (k_team).  p, next_depth / next_tag:
+// of the block's first level.
 hipError_t launch_bfs_dstep(const DlArgs& a, uint32_t* bm, int p, int32_t* depth, int32_t* parent,
-                            const int32_t* perm, int32_t next_depth, int n_blocks, hipStream_t st);
+                            const int32_t* perm, int32_t next_depth, bool team, int n_blocks,
+                            hipStream_t st);
 hipError_t launch_sssp_dstep(const DlArgs& a, const uint32_t* W, unsigned long long* keys,
-                             int32_t* tags, const int32_t* perm, int32_t next_tag, int n_blocks,
-                             hipStream_t st);
+                             int32_t* tags, const int32_t* perm, int32_t next_tag, bool team,
+                             int n_blocks, hipStream_t st);
 // SSSP with the two-level priority queue: improved vertices with dist < T go
 // to the next frontier, the others to far pile `fc` (once per epoch).
 struct PqState {
@@ -581,8 +602,8 @@ hipError_t launch_sssp_pq_relax(int mode, const int32_t* frontier, const int32_t
 hipError_t launch_sssp_pq_refill(const unsigned long long* keys, const PqState& pq, Ctrl* ctrl,
                                  int64_t max_n, int32_t* out_q, uint32_t* out_count, hipStream_t st);
 hipError_t launch_sssp_pq_dstep(const DlArgs& a, const uint32_t* W, unsigned long long* keys,
-                                int32_t* tags, int32_t next_tag, const PqState& pq, int n_blocks,
-                                hipStream_t st);
+                                int32_t* tags, int32_t next_tag, const PqState& pq, bool team,
+                                int n_blocks, hipStream_t st);
 
 // The SSSP distance mirror: one byte per vertex, ceil(dist / 2^shift) of an
 // earlier moment (255: unknown or too large), an upper bound of the distance

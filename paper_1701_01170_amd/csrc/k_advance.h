@@ -101,17 +101,14 @@ constexpr int lb_cap(int chunk_edges) {
   return chunk_edges / 2 < 256 ? 256 : (chunk_edges / 2 > 2048 ? 2048 : chunk_edges / 2);
 }
 
-// Process up to B edges per lane: ok[r] marks a real edge (u[r], pay[r], ce[r]).
-// All 64 lanes must take part.  With AGG the whole workgroup appends with one
-// atomic (every thread of the workgroup must then call it the same number of
-// times): a single queue tail shared by the whole grid serialises its
-// atomics, so fewer of them is the point.
-template <class F, int B, bool AGG = false, int BLOCK = kAdvBlock>
-__device__ __forceinline__ void edge_batch(const F& f, const int32_t* __restrict__ C, bool (&ok)[B],
-                                           const int32_t (&u)[B], const typename F::pay_t (&pay)[B],
-                                           const int32_t (&ce)[B], int32_t* __restrict__ out_q,
-                                           uint32_t* __restrict__ out_count) {
-  int32_t v[B];
+// Relax up to B edges per lane: ok[r] marks a real edge (u[r], pay[r], ce[r]) and
+// on return an edge whose end v[r] joins the output (far-pile entries are appended
+// here).  Returns the lane's number of output entries.  All 64 lanes must take part.
+template <class F, int B>
+__device__ __forceinline__ uint32_t edge_commit(const F& f, const int32_t* __restrict__ C,
+                                                bool (&ok)[B], const int32_t (&u)[B],
+                                                const typename F::pay_t (&pay)[B],
+                                                const int32_t (&ce)[B], int32_t (&v)[B]) {
   uint32_t ev[B];
 #pragma unroll
   for (int r = 0; r < B; ++r) {
@@ -148,6 +145,20 @@ __device__ __forceinline__ void edge_batch(const F& f, const int32_t* __restrict
         if (far[r]) f.far_q[fbase++] = v[r];
     }
   }
+  return n_app;
+}
+
+// edge_commit, then the output entries appended to out_q.  With AGG the whole
+// workgroup appends with one atomic (every thread of the workgroup must then call
+// it the same number of times): a single queue tail shared by the whole grid
+// serialises its atomics, so fewer of them is the point.
+template <class F, int B, bool AGG = false, int BLOCK = kAdvBlock>
+__device__ __forceinline__ void edge_batch(const F& f, const int32_t* __restrict__ C, bool (&ok)[B],
+                                           const int32_t (&u)[B], const typename F::pay_t (&pay)[B],
+                                           const int32_t (&ce)[B], int32_t* __restrict__ out_q,
+                                           uint32_t* __restrict__ out_count) {
+  int32_t v[B];
+  const uint32_t n_app = edge_commit<F, B>(f, C, ok, u, pay, ce, v);
   if constexpr (AGG) {
     uint32_t base = block_append<BLOCK>(n_app, out_count);
 #pragma unroll

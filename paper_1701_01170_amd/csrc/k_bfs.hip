@@ -33,7 +33,9 @@ __device__ __forceinline__ int32_t caller_id(const int32_t* perm, int32_t v) {
   return perm ? perm[v] : v;
 }
 
-template <bool ATOMIC_PARENT>
+// FRESH: for kernels that run several levels (their bitmap reads must not come from
+// an L1 line of an earlier level).
+template <bool ATOMIC_PARENT, bool FRESH = false>
 struct BfsVisit {
   uint32_t* __restrict__ bm;
   int32_t* __restrict__ depth;
@@ -50,8 +52,9 @@ struct BfsVisit {
   }
   __device__ __forceinline__ uint32_t edge_value(int64_t) const { return 0u; }
   __device__ __forceinline__ bool probe(int32_t, int32_t, int32_t v, uint32_t) const {
-    const uint2 x = bm_pair(bm, v >> 5);
-    const uint32_t old = p ? x.y : x.x, live = p ? x.x : x.y;
+    const uint64_t x = load_shared<FRESH>(reinterpret_cast<const uint64_t*>(bm) + (v >> 5));
+    const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+    const uint32_t old = p ? hi : lo, live = p ? lo : hi;
     const uint32_t bit = 1u << (v & 31);
     if (ATOMIC_PARENT) return !(old & bit);
     return !((old | live) & bit);
@@ -87,8 +90,9 @@ struct BfsVisit {
       for (int r = 0; r < B; ++r)
         if (ok[r]) atomicMin(reinterpret_cast<uint32_t*>(&parent[v[r]]), (uint32_t)pu[r]);
     }
+    // (a small level has few edges into one vertex: the read would only add a trip)
 #pragma unroll
-    for (int r = 0; r < B; ++r) w[r] = (ATOMIC_PARENT && ok[r]) ? *live[r] : 0u;
+    for (int r = 0; r < B; ++r) w[r] = (ATOMIC_PARENT && !FRESH && ok[r]) ? *live[r] : 0u;
 #pragma unroll
     for (int r = 0; r < B; ++r) {
       const bool go = ok[r] && !(w[r] & bit[r]);
@@ -107,8 +111,15 @@ struct BfsVisit {
   __device__ __forceinline__ void frontier_vertex(int32_t u) const {
     atomicOr(&bm[2 * (u >> 5) + 1 - p], 1u << (u & 31));
   }
-  __device__ __forceinline__ BfsVisit prepare(const Ctrl*, int) const { return *this; }
+  __device__ __forceinline__ BfsVisit prepare(const Ctrl*, int step) const {
+    BfsVisit g = *this;
+    g.p = p ^ (step & 1);
+    g.next_depth = next_depth + step;
+    return g;
+  }
+  __device__ __forceinline__ BfsVisit next() const { return prepare(nullptr, 1); }
   __device__ __forceinline__ void advance(Ctrl*, int, bool) const {}
+  __device__ __forceinline__ void store(Ctrl*, int) const {}
 };
 
 // Push without returning atomics (for levels that discover many vertices):
@@ -783,9 +794,15 @@ hipError_t launch_bfs_pull_list(const int32_t* list, const uint32_t* n_list, int
 }
 
 hipError_t launch_bfs_dstep(const DlArgs& a, uint32_t* bm, int p, int32_t* depth, int32_t* parent,
-                            const int32_t* perm, int32_t next_depth, int n_blocks, hipStream_t st) {
-  const BfsVisit<true> f{bm, depth, parent, perm, next_depth, p};
-  k_dstep<BfsVisit<true>><<<n_blocks, kAdvBlock, 0, st>>>(a, f);
+                            const int32_t* perm, int32_t next_depth, bool team, int n_blocks,
+                            hipStream_t st) {
+  if (team) {
+    const BfsVisit<true, true> f{bm, depth, parent, perm, next_depth, p};
+    k_team<BfsVisit<true, true>><<<n_blocks, kAdvBlock, 0, st>>>(a, f);
+  } else {
+    const BfsVisit<true> f{bm, depth, parent, perm, next_depth, p};
+    k_dstep<BfsVisit<true>><<<n_blocks, kAdvBlock, 0, st>>>(a, f);
+  }
   return hipGetLastError();
 }
 

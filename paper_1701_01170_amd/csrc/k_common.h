@@ -173,4 +173,12 @@ __device__ __forceinline__ bool bm_test(const uint32_t* bm, int32_t v) {
   return (bm[v >> 5] >> (v & 31)) & 1u;
 }
 
+// A load of data that other workgroups change during the kernel.  FRESH: past the
+// CU's own L1 (which no store of another CU updates); otherwise an ordinary load.
+template <bool FRESH, typename T>
+__device__ __forceinline__ T load_shared(const T* p) {
+  if constexpr (FRESH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else return *p;
+}
+
 }  // namespace gr

@@ -297,14 +297,20 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, int6
 // Start of a device-predicated block whose first frontier is queue cur: the
 // block counters, the visited counts before that frontier and the priority
 // queue state of its first step.
-__global__ void k_dl_begin(Ctrl* __restrict__ ctrl, int cur, int64_t vm, int64_t vn,
-                           uint32_t pq_T, int32_t pq_epoch, int32_t pq_fc, int64_t mf) {
+__global__ __launch_bounds__(kStatsGrid) void k_dl_begin(Ctrl* __restrict__ ctrl, int cur,
+                                                         int64_t vm, int64_t vn, uint32_t pq_T,
+                                                         int32_t pq_epoch, int32_t pq_fc,
+                                                         int64_t mf, int64_t* __restrict__ team) {
+  if (team) team[threadIdx.x] = 0;
+  if (threadIdx.x != 0) return;
   ctrl->dl_levels = 0;
   ctrl->dl_stop = 0;
   ctrl->q_count[(cur + 1) % 3] = 0;
   ctrl->dl_vm[0] = vm;
   ctrl->dl_vn[0] = vn;
   ctrl->dl_mf[0] = mf;
+  ctrl->dl_step[0] = ctrl->dl_step[1] = 0;
+  ctrl->dl_fail = 0;
   ctrl->pq_T[0] = pq_T;
   ctrl->pq_epoch[0] = pq_epoch;
   ctrl->pq_fc[0] = pq_fc;
@@ -356,8 +362,9 @@ hipError_t launch_frontier_offsets(const int32_t* frontier, int64_t n_f, const i
 }
 
 hipError_t launch_dl_begin(Ctrl* ctrl, int cur, int64_t vm, int64_t vn, uint32_t pq_T,
-                           int32_t pq_epoch, int32_t pq_fc, hipStream_t st, int64_t mf) {
-  k_dl_begin<<<1, 1, 0, st>>>(ctrl, cur, vm, vn, pq_T, pq_epoch, pq_fc, mf);
+                           int32_t pq_epoch, int32_t pq_fc, hipStream_t st, int64_t mf,
+                           int64_t* team) {
+  k_dl_begin<<<1, team ? kStatsGrid : 1, 0, st>>>(ctrl, cur, vm, vn, pq_T, pq_epoch, pq_fc, mf, team);
   return hipGetLastError();
 }
 

@@ -34,6 +34,9 @@ __device__ __forceinline__ uint32_t caller_id(const int32_t* perm, int32_t u) {
   return (uint32_t)(perm ? perm[u] : u);
 }
 
+// FRESH: for kernels that run several iterations (their key reads must not come from
+// an L1 line of an earlier one).
+template <bool FRESH = false>
 struct SsspVisit {
   const uint32_t* __restrict__ W;
   unsigned long long* __restrict__ keys;
@@ -45,13 +48,15 @@ struct SsspVisit {
   static constexpr bool kFar = false;
   static constexpr bool kBatchCommit = true;
   __device__ __forceinline__ int32_t seg_payload(int32_t u) const {
-    return (int32_t)(uint32_t)(keys[u] >> 32);
+    return (int32_t)(uint32_t)(load_shared<FRESH>(&keys[u]) >> 32);
   }
   __device__ __forceinline__ uint32_t edge_value(int64_t e) const { return W[e]; }
   __device__ __forceinline__ bool probe(int32_t, int32_t du, int32_t v, uint32_t w) const {
     const uint64_t cand = (uint64_t)(uint32_t)du + (uint64_t)w;
     if (cand >= 0xffffffffull) return false;  // cannot be a shortest distance (range checked at entry)
-    return cand <= (keys[v] >> 32);            // keys only decrease: otherwise nothing to gain
+    // keys only decrease: otherwise nothing to gain (FRESH, small iterations: the
+    // atomic minimum itself answers, one trip less)
+    return FRESH || cand <= (keys[v] >> 32);
   }
   __device__ __forceinline__ bool commit(int32_t u, int32_t du, int32_t v, uint32_t w) const {
     const uint64_t cand = (uint64_t)(uint32_t)du + (uint64_t)w;
@@ -82,8 +87,14 @@ struct SsspVisit {
     for (int r = 0; r < B; ++r) code[r] = prev[r] != next_tag;
   }
   __device__ __forceinline__ void frontier_vertex(int32_t) const {}
-  __device__ __forceinline__ SsspVisit prepare(const Ctrl*, int) const { return *this; }
+  __device__ __forceinline__ SsspVisit prepare(const Ctrl*, int step) const {
+    SsspVisit g = *this;
+    g.next_tag = next_tag + step;
+    return g;
+  }
+  __device__ __forceinline__ SsspVisit next() const { return prepare(nullptr, 1); }
   __device__ __forceinline__ void advance(Ctrl*, int, bool) const {}
+  __device__ __forceinline__ void store(Ctrl*, int) const {}
 };
 
 // Relaxation without a returning atomic (for iterations with many frontier
@@ -503,35 +514,37 @@ __device__ __forceinline__ uint32_t pq_next_threshold(uint32_t T, uint32_t delta
 }
 
 // Split far pile fc into the next frontier and far pile (fc + 1) % 3 (see the
-// file comment).  Grid-stride over kRefillItems entries per thread; both
-// lists are appended with one atomic per workgroup and round, so every thread
-// of the workgroup must call it.
+// file comment).  Workgroup `wg` of `n_wg` in a stride loop over kRefillItems
+// entries per thread; both lists are appended with one atomic per workgroup and
+// round, so every thread of the workgroup must call it.
 constexpr int kRefillItems = 4;
+template <bool FRESH>
 __device__ __forceinline__ void pq_refill_pass(const unsigned long long* __restrict__ keys,
                                                uint32_t T, uint32_t delta, int32_t epoch, int32_t fc,
                                                int32_t* __restrict__ far_base,
                                                int32_t* __restrict__ far_tag, int64_t V, Ctrl* ctrl,
-                                               int32_t* __restrict__ out_q, uint32_t* out_count) {
+                                               int32_t* __restrict__ out_q, uint32_t* out_count,
+                                               int wg, int n_wg) {
   constexpr int K = kRefillItems;
   const uint32_t T1 = pq_next_threshold(T, delta);
   const int32_t fn = (fc + 1) % 3;
   const int32_t* __restrict__ in = far_base + (int64_t)fc * V;
   int32_t* __restrict__ keep_q = far_base + (int64_t)fn * V;
-  const int64_t n = ctrl->far_count[fc];
+  const int64_t n = load_shared<FRESH>(&ctrl->far_count[fc]);
   const int64_t per_round = (int64_t)kAdvBlock * K;
-  const int64_t stride = (int64_t)gridDim.x * per_round;
-  for (int64_t base = (int64_t)blockIdx.x * per_round; base < n; base += stride) {
+  const int64_t stride = (int64_t)n_wg * per_round;
+  for (int64_t base = (int64_t)wg * per_round; base < n; base += stride) {
     int32_t v[K];
     bool near[K], keep[K];
     uint32_t n_near = 0, n_keep = 0;
 #pragma unroll
     for (int r = 0; r < K; ++r) {
       const int64_t i = base + r * kAdvBlock + threadIdx.x;
-      v[r] = i < n ? in[i] : -1;
+      v[r] = i < n ? load_shared<FRESH>(&in[i]) : -1;
     }
 #pragma unroll
     for (int r = 0; r < K; ++r) {
-      const uint32_t d = v[r] >= 0 ? (uint32_t)(keys[v[r]] >> 32) : 0u;
+      const uint32_t d = v[r] >= 0 ? (uint32_t)(load_shared<FRESH>(&keys[v[r]]) >> 32) : 0u;
       near[r] = v[r] >= 0 && d >= T && d < T1;
       keep[r] = v[r] >= 0 && d >= T1;
       if (keep[r]) far_tag[v[r]] = epoch + 1;
@@ -548,6 +561,7 @@ __device__ __forceinline__ void pq_refill_pass(const unsigned long long* __restr
   }
 }
 
+template <bool FRESH = false>
 struct SsspPqVisit {
   const uint32_t* __restrict__ W;
   unsigned long long* __restrict__ keys;
@@ -568,13 +582,13 @@ struct SsspPqVisit {
   static constexpr bool kFar = true;
   static constexpr bool kBatchCommit = true;
   __device__ __forceinline__ int32_t seg_payload(int32_t u) const {
-    return (int32_t)(uint32_t)(keys[u] >> 32);
+    return (int32_t)(uint32_t)(load_shared<FRESH>(&keys[u]) >> 32);
   }
   __device__ __forceinline__ uint32_t edge_value(int64_t e) const { return W[e]; }
   __device__ __forceinline__ bool probe(int32_t, int32_t du, int32_t v, uint32_t w) const {
     const uint64_t cand = (uint64_t)(uint32_t)du + (uint64_t)w;
     if (cand >= 0xffffffffull) return false;
-    return cand <= (keys[v] >> 32);
+    return FRESH || cand <= (keys[v] >> 32);
   }
   // 1: next frontier, 2: far pile, 0: nothing to append
   __device__ __forceinline__ int commit(int32_t u, int32_t du, int32_t v, uint32_t w) const {
@@ -613,6 +627,7 @@ struct SsspPqVisit {
   __device__ __forceinline__ SsspPqVisit prepare(Ctrl* ctrl, int step) const {
     SsspPqVisit g = *this;
     const int s = step & 1;
+    g.next_tag = next_tag + step;
     g.T = ctrl->pq_T[s];
     g.epoch = ctrl->pq_epoch[s];
     g.fc = ctrl->pq_fc[s];
@@ -620,11 +635,16 @@ struct SsspPqVisit {
     g.far_count = &ctrl->far_count[g.fc];
     return g;
   }
+  __device__ __forceinline__ SsspPqVisit next() const {
+    SsspPqVisit g = *this;
+    g.next_tag = next_tag + 1;
+    return g;
+  }
   // a refill step inside a device-predicated block runs on that block's small
   // grid, so only modest far piles are split there; larger ones end the block
   // and are split by the full-grid refill kernel
   __device__ __forceinline__ bool far_pending(const Ctrl* ctrl) const {
-    const uint32_t n = ctrl->far_count[fc];
+    const uint32_t n = load_shared<FRESH>(&ctrl->far_count[fc]);
     return n > 0 && n <= kDlMaxRefill;
   }
   // queue state of the next step (called once, by one thread)
@@ -641,8 +661,27 @@ struct SsspPqVisit {
       ctrl->pq_fc[s] = fc;
     }
   }
-  __device__ __forceinline__ void refill(Ctrl* ctrl, int32_t* out_q, uint32_t* out_count) const {
-    pq_refill_pass(keys, T, delta, epoch, fc, far_base, far_tag, V, ctrl, out_q, out_count);
+  __device__ __forceinline__ void refill(Ctrl* ctrl, int32_t* out_q, uint32_t* out_count, int wg,
+                                         int n_wg) const {
+    pq_refill_pass<FRESH>(keys, T, delta, epoch, fc, far_base, far_tag, V, ctrl, out_q, out_count, wg, n_wg);
+  }
+  // the same for a kernel that runs several steps: the pile the refill after this
+  // one fills starts empty; the queue state after a refill; the state kept as that
+  // of `step`
+  __device__ __forceinline__ void clear_far(Ctrl* ctrl) const { ctrl->far_count[(fc + 2) % 3] = 0; }
+  __device__ __forceinline__ SsspPqVisit after_refill() const {
+    SsspPqVisit g = next();
+    g.T = pq_next_threshold(T, delta);
+    g.epoch = epoch + 1;
+    g.fc = (fc + 1) % 3;
+    g.far_q = far_base + (int64_t)g.fc * V;
+    g.far_count = far_count - fc + g.fc;
+    return g;
+  }
+  __device__ __forceinline__ void store(Ctrl* ctrl, int step) const {
+    ctrl->pq_T[step & 1] = T;
+    ctrl->pq_epoch[step & 1] = epoch;
+    ctrl->pq_fc[step & 1] = fc;
   }
 };
 
@@ -651,8 +690,8 @@ __global__ __launch_bounds__(kAdvBlock) void k_sssp_pq_refill(const unsigned lon
                                                         int32_t* __restrict__ out_q,
                                                         uint32_t* __restrict__ out_count) {
   if (blockIdx.x == 0 && threadIdx.x == 0) ctrl->far_count[(pq.fc + 2) % 3] = 0;
-  pq_refill_pass(keys, pq.T, pq.delta, pq.epoch, pq.fc, pq.far_base, pq.far_tag, pq.V, ctrl, out_q,
-                 out_count);
+  pq_refill_pass<false>(keys, pq.T, pq.delta, pq.epoch, pq.fc, pq.far_base, pq.far_tag, pq.V, ctrl, out_q,
+                 out_count, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(256) void k_sssp_init(unsigned long long* __restrict__ keys,
@@ -776,7 +815,7 @@ hipError_t launch_sssp_relax(int mode, const int32_t* frontier, const int32_t* o
                              unsigned long long* keys, int32_t* tags, const int32_t* perm,
                              int32_t next_tag, int32_t* out_q, uint32_t* out_count, const AdvCfg& cfg,
                              hipStream_t st) {
-  SsspVisit f{W, keys, tags, perm, next_tag};
+  SsspVisit<> f{W, keys, tags, perm, next_tag};
   return push_dispatch(mode, frontier, offsets, rstart, chunk_start, n_f, m_f, R, C, f, out_q,
                        out_count, cfg, st);
 }
@@ -796,20 +835,25 @@ hipError_t launch_sssp_finalize(const unsigned long long* keys, const int32_t* R
 }
 
 hipError_t launch_sssp_dstep(const DlArgs& a, const uint32_t* W, unsigned long long* keys,
-                             int32_t* tags, const int32_t* perm, int32_t next_tag, int n_blocks,
-                             hipStream_t st) {
-  const SsspVisit f{W, keys, tags, perm, next_tag};
-  k_dstep<SsspVisit><<<n_blocks, kAdvBlock, 0, st>>>(a, f);
+                             int32_t* tags, const int32_t* perm, int32_t next_tag, bool team,
+                             int n_blocks, hipStream_t st) {
+  if (team)
+    k_team<SsspVisit<true>><<<n_blocks, kAdvBlock, 0, st>>>(
+        a, SsspVisit<true>{W, keys, tags, perm, next_tag});
+  else
+    k_dstep<SsspVisit<>><<<n_blocks, kAdvBlock, 0, st>>>(
+        a, SsspVisit<>{W, keys, tags, perm, next_tag});
   return hipGetLastError();
 }
 
 namespace {
-SsspPqVisit pq_functor(const uint32_t* W, unsigned long long* keys, int32_t* tags, int32_t next_tag,
-                       const PqState& pq, Ctrl* ctrl) {
-  return SsspPqVisit{W,          keys,     tags,          next_tag,
-                     pq.T,       pq.delta, pq.epoch,      pq.fc,
-                     pq.far_base, pq.far_tag, pq.V,     pq.far_base + (int64_t)pq.fc * pq.V,
-                     &ctrl->far_count[pq.fc], pq.perm};
+template <bool FRESH>
+SsspPqVisit<FRESH> pq_functor(const uint32_t* W, unsigned long long* keys, int32_t* tags,
+                              int32_t next_tag, const PqState& pq, Ctrl* ctrl) {
+  return SsspPqVisit<FRESH>{W,           keys,       tags,     next_tag,
+                            pq.T,        pq.delta,   pq.epoch, pq.fc,
+                            pq.far_base, pq.far_tag, pq.V,     pq.far_base + (int64_t)pq.fc * pq.V,
+                            &ctrl->far_count[pq.fc], pq.perm};
 }
 }  // namespace
 
@@ -819,7 +863,7 @@ hipError_t launch_sssp_pq_relax(int mode, const int32_t* frontier, const int32_t
                                 unsigned long long* keys, int32_t* tags, int32_t next_tag,
                                 const PqState& pq, Ctrl* ctrl, int32_t* out_q, uint32_t* out_count,
                                 const AdvCfg& cfg, hipStream_t st) {
-  const SsspPqVisit f = pq_functor(W, keys, tags, next_tag, pq, ctrl);
+  const SsspPqVisit<> f = pq_functor<false>(W, keys, tags, next_tag, pq, ctrl);
   return push_dispatch(mode, frontier, offsets, rstart, chunk_start, n_f, m_f, R, C, f, out_q,
                        out_count, cfg, st);
 }
@@ -833,10 +877,14 @@ hipError_t launch_sssp_pq_refill(const unsigned long long* keys, const PqState& 
 }
 
 hipError_t launch_sssp_pq_dstep(const DlArgs& a, const uint32_t* W, unsigned long long* keys,
-                                int32_t* tags, int32_t next_tag, const PqState& pq, int n_blocks,
-                                hipStream_t st) {
-  const SsspPqVisit f = pq_functor(W, keys, tags, next_tag, pq, a.ctrl);
-  k_dstep<SsspPqVisit><<<n_blocks, kAdvBlock, 0, st>>>(a, f);
+                                int32_t* tags, int32_t next_tag, const PqState& pq, bool team,
+                                int n_blocks, hipStream_t st) {
+  if (team)
+    k_team<SsspPqVisit<true>><<<n_blocks, kAdvBlock, 0, st>>>(
+        a, pq_functor<true>(W, keys, tags, next_tag, pq, a.ctrl));
+  else
+    k_dstep<SsspPqVisit<>><<<n_blocks, kAdvBlock, 0, st>>>(
+        a, pq_functor<false>(W, keys, tags, next_tag, pq, a.ctrl));
   return hipGetLastError();
 }
 
