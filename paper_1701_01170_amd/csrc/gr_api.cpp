@@ -966,8 +966,6 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
   GR_HIP(hipEventRecord(ctx->ev_start, st));
   GR_HIP(launch_bfs_init(depth, parent, V, bm, NW, src, qA, ctrl, st));
   int cur = 0, sp = 0, p = 0;
-  GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
-                               &ctrl->q_count[(cur + 1) % 3], nullptr, st));
   const bool learned = opts.policy == GR_POLICY_LEARNED && ctx->policy_loaded;
   const float* mlp = static_cast<const float*>(ctx->pool[S_MLP].ptr);
   const int allowed = pull_ok ? 0xF : 0x3;
@@ -976,22 +974,42 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
     return MlpSelect{mlp, slot, V, E, n_u, m_u, prev_pull, allowed};
   };
   MlpSelect msel = select_at(sp, V, E, 0);
-  GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
+  DlPlan dl;
+  GR_TRY(dl_plan(ctx, ar, g, opts, learned, tracing, &dl));
+  // A level that fits a block is pushed whatever its statistics say, so where no
+  // network asks for them the first block starts at once: its kernels find on the
+  // device whether the source's row fits, and the statistics come with its
+  // read-back (one host round trip less).
+  bool known = !dl.on || learned ||
+               (opts.policy == GR_POLICY_FIXED && opts.fixed_action >= GR_PULL_TWC && pull_ok);
+  if (known) {
+    GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
+                                 &ctrl->q_count[(cur + 1) % 3], nullptr, st));
+    GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
+  }
 
   Selector sel;
   sel.init(opts, g->V, g->E, pull_ok, /*is_sssp=*/false, ctx->policy_loaded);
   LevelFeatures lf{};
   lf.V = V;
   lf.E = E;
-  int64_t n_f = hc->n_f[sp], m_f = hc->m_f[sp], max_deg = hc->max_deg[sp];
-  int64_t visited_n = n_f, visited_m = m_f;
+  int64_t n_f = 1, m_f = 0, max_deg = 0;  // m_f, max_deg: 0 until known
+  int64_t visited_n = 0, visited_m = 0;
+  auto take_stats = [&]() {
+    n_f = hc->n_f[sp];
+    m_f = hc->m_f[sp];
+    max_deg = hc->max_deg[sp];
+    visited_n += n_f;
+    visited_m += m_f;
+    known = true;
+  };
+  if (known) take_stats();
+  else visited_n = 1;
   int64_t inspected_push = 0;
   int64_t pull_in = 0;     // input vertices of the last pull level (trace)
   int64_t pull_seen = 0;   // the device's pull neighbour count before this level
   int level = 0;
   gr_run_stats rs{};
-  DlPlan dl;
-  GR_TRY(dl_plan(ctx, ar, g, opts, learned, tracing, &dl));
 
   while (n_f > 0 && (opts.max_iterations <= 0 || level < opts.max_iterations)) {
     lf.level = level;
@@ -1073,11 +1091,12 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
                                       block_ms / k, StepWork{li.n_f, li.m_f}));
           }
         }
-        n_f = hc->n_f[sp];
-        m_f = hc->m_f[sp];
-        max_deg = hc->max_deg[sp];
-        visited_n += n_f;
-        visited_m += m_f;
+        take_stats();
+        continue;
+      }
+      if (!known) {  // the source's row is longer than a block takes
+        visited_n = visited_m = 0;
+        take_stats();
         continue;
       }
     }
@@ -1187,11 +1206,7 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
       GR_TRY(record_trace(ctx, opts_in, lf, action, kernel, hc->n_f[sp], w));
     }
     pull_seen = hc->inspected;
-    n_f = hc->n_f[sp];
-    m_f = hc->m_f[sp];
-    max_deg = hc->max_deg[sp];
-    visited_n += n_f;
-    visited_m += m_f;
+    take_stats();
   }
   if (perm && !internal_ids)
     GR_HIP(launch_permute_out(g->inv, V, depth, parent, out_depth, out_parent, st));
@@ -1334,38 +1349,58 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
   Ctrl* hc = ctx->host_ctrl;
   int32_t* q[3] = {qA, qB, qC};
 
-  GR_HIP(hipMemcpyAsync(src_dev, src_both.data(), sizeof(int32_t) * 2 * n_src,
-                        hipMemcpyHostToDevice, st));
-  GR_HIP(hipMemcpyAsync(qA, src_both.data(), sizeof(int32_t) * n_src, hipMemcpyHostToDevice, st));
-  GR_HIP(hipStreamSynchronize(st));  // the host vector must outlive the copies
+  const bool learned = opts.policy == GR_POLICY_LEARNED && ctx->policy_loaded;
+  const float* mlp = static_cast<const float*>(ctx->pool[S_MLP].ptr);
+  const bool tracing = opts_in && opts_in->trace;
+  DlPlan dl;
+  Arena ar;
+  ar.ctx = ctx;
+  GR_TRY(dl_plan(ctx, ar, g, opts, learned, tracing, &dl));
+  // few sources travel as kernel arguments, more through copies (which the host
+  // vector must outlive)
+  SourceArgs by_value;
+  by_value.n = 0;
+  if (n_src <= kSourceArgs) {
+    by_value.n = n_src;
+    std::copy(src_both.begin(), src_both.end(), by_value.v);
+  } else {
+    GR_HIP(hipMemcpyAsync(src_dev, src_both.data(), sizeof(int32_t) * 2 * n_src,
+                          hipMemcpyHostToDevice, st));
+    GR_HIP(hipMemcpyAsync(qA, src_both.data(), sizeof(int32_t) * n_src, hipMemcpyHostToDevice, st));
+    GR_HIP(hipStreamSynchronize(st));
+  }
   GR_HIP(hipEventRecord(ctx->ev_start, st));
   GR_HIP(launch_sssp_init(keys, tags, use_pq ? pq.far_tag : nullptr, mirror, relaxed, bins.state,
                           V, ctrl, st));
-  GR_HIP(launch_sssp_seed(src_dev, n_src, keys, tags, ctrl, st));
+  GR_HIP(launch_sssp_seed(by_value, src_dev, n_src, keys, tags, qA, ctrl, st));
   int cur = 0, sp = 0;
-  GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
-                               &ctrl->q_count[(cur + 1) % 3], nullptr, st));
-  const bool learned = opts.policy == GR_POLICY_LEARNED && ctx->policy_loaded;
-  const float* mlp = static_cast<const float*>(ctx->pool[S_MLP].ptr);
   MlpSelect msel{mlp, sp, V, E, 0, 0, 0, 0x3};
-  GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
+  // as in gr_bfs: the first block starts without waiting for the statistics
+  bool known = !dl.on || learned || n_src > kDlMaxN;
+  if (known) {
+    GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
+                                 &ctrl->q_count[(cur + 1) % 3], nullptr, st));
+    GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
+  }
 
   Selector sel;
   sel.init(opts, V, E, /*pull_ok=*/false, /*is_sssp=*/true, ctx->policy_loaded);
   LevelFeatures lf{};
   lf.V = V;
   lf.E = E;
-  int64_t n_f = hc->n_f[sp], m_f = hc->m_f[sp], max_deg = hc->max_deg[sp];
+  int64_t n_f = n_src, m_f = 0, max_deg = 0;  // m_f, max_deg: 0 until known
+  auto take_stats = [&]() {
+    n_f = hc->n_f[sp];
+    m_f = hc->m_f[sp];
+    max_deg = hc->max_deg[sp];
+    known = true;
+  };
+  if (known) take_stats();
   int64_t far_n = 0;
   int it = 0;
   int64_t inspected = 0;
   int64_t expanded = 0;  // sum of the frontier sizes so far
   gr_run_stats rs{};
-  const bool tracing = opts_in && opts_in->trace;
-  DlPlan dl;
-  Arena ar;
-  ar.ctx = ctx;
-  GR_TRY(dl_plan(ctx, ar, g, opts, learned, tracing, &dl));
   // after a step that produced the frontier in q[cur]: statistics, selector, read-back
   // with load-balanced advance likely (average degree), the degree scan of
   // each new frontier is queued ahead of the read-back (offsets_ready)
@@ -1468,9 +1503,11 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
                                       block_ms / k, StepWork{li.n_f, li.m_f}));
           }
         }
-        n_f = hc->n_f[sp];
-        m_f = hc->m_f[sp];
-        max_deg = hc->max_deg[sp];
+        take_stats();
+        continue;
+      }
+      if (!known) {  // the sources' rows are longer than a block takes
+        take_stats();
         continue;
       }
     }
@@ -1539,9 +1576,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
     if (tracing)
       GR_TRY(record_trace(ctx, opts_in, lf, action, kernel, hc->n_f[sp],
                           kernel == kTraceKernelRefill ? StepWork{refill_in, 0} : StepWork{n_f, m_f}));
-    n_f = hc->n_f[sp];
-    m_f = hc->m_f[sp];
-    max_deg = hc->max_deg[sp];
+    take_stats();
   }
   int64_t* reached = &ctrl->reached_edges;
   GR_HIP(launch_sssp_finalize(keys, perm ? g->R_orig : g->R, V, dist, pred, perm ? g->inv : nullptr,
@@ -1588,7 +1623,7 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
   using u64 = unsigned long long;
 
   u64 *visit, *front[2], *next;
-  int32_t *qA, *qB, *qC, *offsets, *rstart, *chunks, *src_dev;
+  int32_t *qA, *qB, *qC, *offsets, *rstart, *chunks;
   int64_t* bsums;
   Ctrl* ctrl;
   GR_TRY(pool_typed(ctx, S_MASK_A, V, &visit));
@@ -1603,7 +1638,6 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
   GR_TRY(pool_typed(ctx, S_CHUNKS, E / 512 + 2, &chunks));
   GR_TRY(pool_typed(ctx, S_BLOCK_SUMS, G + 1, &bsums));
   GR_TRY(pool_typed(ctx, S_CTRL, 1, &ctrl));
-  GR_TRY(pool_typed(ctx, S_TMP0, 128, &src_dev));  // traversal ids, then caller ids
   Ctrl* hc = ctx->host_ctrl;
   int32_t* q[3] = {qA, qB, qC};
 
@@ -1660,11 +1694,13 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
       if (ppass)
         GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(ppass), (int64_t)kk * V, 0xffffffffu, st));
     }
-    GR_HIP(hipMemcpyAsync(src_dev, srcs.data(), sizeof(int32_t) * 2 * kk, hipMemcpyHostToDevice, st));
-    GR_HIP(hipMemcpyAsync(qA, uniq.data(), sizeof(int32_t) * uniq.size(), hipMemcpyHostToDevice, st));
+    SourceArgs by_value;  // the pass's sources, then the distinct ones
+    by_value.n = kk;
+    std::copy(srcs.begin(), srcs.end(), by_value.v);
+    std::copy(uniq.begin(), uniq.end(), by_value.v + 2 * kk);
     GR_HIP(launch_ms_init(visit, front[0], front[1], next, out, V, (int32_t)uniq.size(), ctrl, st));
-    GR_HIP(launch_ms_seed(src_dev, src_dev + kk, kk, visit, front[0], planes ? nullptr : dpass, V,
-                          g->R, ctrl, st));
+    GR_HIP(launch_ms_seed(by_value, (int32_t)uniq.size(), visit, front[0], planes ? nullptr : dpass,
+                          V, g->R, qA, ctrl, st));
     // the next depth no longer fits the planes: write out what there is and go
     // on in the caller's arrays
     auto leave_planes = [&]() -> gr_status {
@@ -1684,7 +1720,6 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
     GR_HIP(launch_frontier_stats(q[cur], &ctrl->q_count[cur], g->R, bsums, ctrl, sp,
                                  &ctrl->q_count[(cur + 1) % 3], nullptr, st));
     MlpSelect msel = select_at(sp);
-    // (the read-back also keeps the host source vectors alive for the copies)
     GR_TRY(read_ctrl(ctx, ctrl, st, StatsSum{bsums, sp}, learned ? &msel : nullptr));
     int64_t n_a = hc->n_f[sp], m_a = hc->m_f[sp];
     while (n_a > 0 && (opts.max_iterations <= 0 || level < opts.max_iterations)) {

@@ -191,6 +191,15 @@ namespace gr {
 
 gr_status pool_get(gr_ctx* ctx, Slot s, size_t bytes, void** out);
 
+// Host-given sources passed by value: n traversal ids, n caller ids and, for the
+// batched BFS, the distinct traversal ids.  n = 0: the sources are in device memory.
+constexpr int kSourceArgs = 256;
+struct SourceArgs {
+  int32_t n;
+  int32_t v[2 * kSourceArgs];
+};
+static_assert(3 * 64 <= 2 * kSourceArgs, "a batched pass's sources fit");
+
 // Launch shape of the push-advance kernels (tuning knobs: the results never
 // depend on them).
 struct AdvCfg {
@@ -423,9 +432,9 @@ hipError_t launch_msssp_finalize(const unsigned long long* keys, int KS, int32_t
 
 // multi-source BFS (64-bit source masks per vertex); depth / parent are the
 // caller's [k][V] arrays in caller ids (perm nullable)
-hipError_t launch_ms_seed(const int32_t* src_dev, const int32_t* src_orig_dev, int32_t k,
-                          unsigned long long* visit, unsigned long long* front, int32_t* depth,
-                          int64_t V, const int32_t* R, Ctrl* ctrl, hipStream_t st);
+hipError_t launch_ms_seed(const SourceArgs& src, int32_t n_uniq, unsigned long long* visit,
+                          unsigned long long* front, int32_t* depth, int64_t V, const int32_t* R,
+                          int32_t* queue, Ctrl* ctrl, hipStream_t st);
 // Where a pass's results go while it runs.  planes != null: depths as bit planes
 // ([V][kMsPlanes] words, depths below 1 << kMsPlanes) and parents in rows of
 // 1 << kp_log words (prow, null when not wanted), turned into the caller's
@@ -626,8 +635,11 @@ inline uint32_t mirror_shift_for(uint32_t max_weight) {
 hipError_t launch_sssp_init(unsigned long long* keys, int32_t* tags, int32_t* far_tag,
                             DistMirror mirror, uint32_t* relaxed, uint32_t* bin_state, int64_t V,
                             Ctrl* ctrl, hipStream_t st);
-hipError_t launch_sssp_seed(const int32_t* src_dev, int32_t n, unsigned long long* keys,
-                            int32_t* tags, Ctrl* ctrl, hipStream_t st);
+// sources by value (copied to src_dev and the first queue) or, with by_value.n = 0,
+// already there
+hipError_t launch_sssp_seed(const SourceArgs& by_value, int32_t* src_dev, int32_t n,
+                            unsigned long long* keys, int32_t* tags, int32_t* queue, Ctrl* ctrl,
+                            hipStream_t st);
 // keys hold (dist << 32 | predecessor in caller ids); perm nullable
 hipError_t launch_sssp_relax(int mode, const int32_t* frontier, const int32_t* offsets,
                              const int32_t* rstart, const int32_t* chunk_start, int64_t n_f,

@@ -452,7 +452,7 @@ __global__ __launch_bounds__(256) void k_ms_output(const u64* __restrict__ visit
 }
 
 // Masks, planes and (nullable) parent rows of a pass cleared, the frontier
-// counters set (the queue already holds the n_src distinct sources).
+// counters set (n_src distinct sources).
 __global__ __launch_bounds__(256) void k_ms_init(u64* __restrict__ visit, u64* __restrict__ f0,
                                                  u64* __restrict__ f1, u64* __restrict__ next,
                                                  u64* __restrict__ planes,
@@ -480,21 +480,22 @@ __global__ __launch_bounds__(256) void k_ms_init(u64* __restrict__ visit, u64* _
 
 // Sources: their bits in visit / front, depth 0 (when the caller's array is
 // written directly), and the reached-pair counters start at the k source pairs.
-__global__ __launch_bounds__(256) void k_ms_seed(const int32_t* __restrict__ src,
-                                                 const int32_t* __restrict__ src_orig, int32_t k,
-                                                 u64* __restrict__ visit, u64* __restrict__ front,
-                                                 int32_t* __restrict__ depth, int64_t V,
-                                                 const int32_t* __restrict__ R,
-                                                 Ctrl* __restrict__ ctrl) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < k) {
-    const int32_t v = src[s];
+__global__ __launch_bounds__(64) void k_ms_seed(SourceArgs a, int32_t n_uniq,
+                                                u64* __restrict__ visit, u64* __restrict__ front,
+                                                int32_t* __restrict__ depth, int64_t V,
+                                                const int32_t* __restrict__ R,
+                                                int32_t* __restrict__ queue,
+                                                Ctrl* __restrict__ ctrl) {
+  const int s = threadIdx.x;
+  if (s < n_uniq) queue[s] = a.v[2 * a.n + s];
+  if (s < a.n) {
+    const int32_t v = a.v[s];
     atomicOr(&visit[v], 1ull << s);
     atomicOr(&front[v], 1ull << s);
-    if (depth) depth[(int64_t)s * V + src_orig[s]] = 0;
+    if (depth) depth[(int64_t)s * V + a.v[a.n + s]] = 0;
     atomicAdd((unsigned long long*)&ctrl->ms_pair_edges, (unsigned long long)(R[v + 1] - R[v]));
   }
-  if (s == 0) atomicAdd((unsigned long long*)&ctrl->ms_pairs, (unsigned long long)k);
+  if (s == 0) atomicAdd((unsigned long long*)&ctrl->ms_pairs, (unsigned long long)a.n);
 }
 
 // sum over v of popcount(visit[v]) * degree(v)
@@ -534,10 +535,10 @@ inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1)
 
 }  // namespace
 
-hipError_t launch_ms_seed(const int32_t* src_dev, const int32_t* src_orig_dev, int32_t k,
-                          u64* visit, u64* front, int32_t* depth, int64_t V, const int32_t* R,
-                          Ctrl* ctrl, hipStream_t st) {
-  k_ms_seed<<<1, 256, 0, st>>>(src_dev, src_orig_dev, k, visit, front, depth, V, R, ctrl);
+hipError_t launch_ms_seed(const SourceArgs& src, int32_t n_uniq, u64* visit, u64* front,
+                          int32_t* depth, int64_t V, const int32_t* R, int32_t* queue, Ctrl* ctrl,
+                          hipStream_t st) {
+  k_ms_seed<<<1, 64, 0, st>>>(src, n_uniq, visit, front, depth, V, R, queue, ctrl);
   return hipGetLastError();
 }
 

@@ -721,16 +721,31 @@ __global__ __launch_bounds__(256) void k_sssp_init(unsigned long long* __restric
 }
 
 // Sources: distance 0, no predecessor; the deduplicated list is frontier 0.
+__device__ __forceinline__ void seed_source(int32_t v, unsigned long long* __restrict__ keys,
+                                            int32_t* __restrict__ tags) {
+  keys[v] = 0xffffffffull;
+  tags[v] = 0;
+}
+
 __global__ __launch_bounds__(256) void k_sssp_seed(const int32_t* __restrict__ src, int32_t n,
                                                    unsigned long long* __restrict__ keys,
                                                    int32_t* __restrict__ tags,
                                                    Ctrl* __restrict__ ctrl) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    keys[src[i]] = 0xffffffffull;
-    tags[src[i]] = 0;
-  }
+  if (i < n) seed_source(src[i], keys, tags);
   if (i == 0) ctrl->q_count[0] = (uint32_t)n;
+}
+
+__global__ __launch_bounds__(kSourceArgs) void k_sssp_seed_args(
+    SourceArgs a, int32_t* __restrict__ src, unsigned long long* __restrict__ keys,
+    int32_t* __restrict__ tags, int32_t* __restrict__ queue, Ctrl* __restrict__ ctrl) {
+  const int i = threadIdx.x;
+  if (i < a.n) {
+    src[i] = queue[i] = a.v[i];
+    src[a.n + i] = a.v[a.n + i];
+    seed_source(a.v[i], keys, tags);
+  }
+  if (i == 0) ctrl->q_count[0] = (uint32_t)a.n;
 }
 
 // dist / pred at caller ids c and the degree sum of the reached vertices.
@@ -803,9 +818,13 @@ hipError_t launch_sssp_init(unsigned long long* keys, int32_t* tags, int32_t* fa
   return hipGetLastError();
 }
 
-hipError_t launch_sssp_seed(const int32_t* src_dev, int32_t n, unsigned long long* keys,
-                            int32_t* tags, Ctrl* ctrl, hipStream_t st) {
-  k_sssp_seed<<<blocks_for(n, 256), 256, 0, st>>>(src_dev, n, keys, tags, ctrl);
+hipError_t launch_sssp_seed(const SourceArgs& by_value, int32_t* src_dev, int32_t n,
+                            unsigned long long* keys, int32_t* tags, int32_t* queue, Ctrl* ctrl,
+                            hipStream_t st) {
+  if (by_value.n > 0)
+    k_sssp_seed_args<<<1, kSourceArgs, 0, st>>>(by_value, src_dev, keys, tags, queue, ctrl);
+  else
+    k_sssp_seed<<<blocks_for(n, 256), 256, 0, st>>>(src_dev, n, keys, tags, ctrl);
   return hipGetLastError();
 }
 
