@@ -727,6 +727,14 @@ constexpr int64_t kSsspMarksDivisor = 16;
 // measured 2.57-2.59 ms with the screen from V / 8, 2.61-2.65 ms from V / 2,
 // 2.76 ms from V and 2.77 ms without it.
 constexpr int64_t kSsspMirrorDivisor = 8;
+// Degree-ordered graphs: iterations with at least kHotMinEdges frontier edges, rows of
+// kHotMinDegree edges on average, relax with the hubs' mirror in LDS
+// (k_sssp_relax_hot).  Below, the table's load (32 MB through the L2s) and the search
+// of an edge's segment cost more than the gathers they save: R-MAT 22's levels of 95 M
+// edges (395 on average) 1.13 -> 0.88 ms, of 54 M (26) 0.44 -> 0.53 ms, of 7.4 M (40)
+// 0.06 -> 0.12 ms.
+constexpr int64_t kHotMinEdges = 1 << 22;
+constexpr int64_t kHotMinDegree = 64;
 
 struct DlPlan {
   bool on = false;
@@ -1540,9 +1548,12 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
         GR_TRY(marks_buffer(ctx, ar, V, &marks, st));
         kernel += kTraceMarksOffset;
         const bool screen = expanded + n_f + far_n >= V / kSsspMirrorDivisor;
+        const int64_t n_hot = perm && mode == 2 && m_f >= kHotMinEdges &&
+                                      m_f >= kHotMinDegree * n_f
+                                  ? std::min<int64_t>(V, kHotVertices) : 0;
         GR_HIP(launch_sssp_relax_marks(mode, q[cur], offsets, rstart, chunks, n_f, m_f, g->R, g->C,
-                                       g->W, keys, perm, marks, mirror, relaxed, screen, adv,
-                                       st));
+                                       g->W, keys, perm, marks, mirror, relaxed, screen, n_hot,
+                                       ctx->cu_count, adv, st));
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k1, st));
         if (use_pq)
           GR_HIP(launch_sssp_pq_mark_compact(marks, V, keys, mirror, relaxed, pq, ctrl,

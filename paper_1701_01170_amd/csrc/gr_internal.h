@@ -647,6 +647,10 @@ hipError_t launch_sssp_relax(int mode, const int32_t* frontier, const int32_t* o
                              unsigned long long* keys, int32_t* tags, const int32_t* perm,
                              int32_t next_tag, int32_t* out_q, uint32_t* out_count, const AdvCfg& cfg,
                              hipStream_t st);
+// Vertices whose mirror k_sssp_relax_hot keeps in LDS (the first ones of a
+// degree-ordered graph).
+constexpr int kHotVertices = 1 << 17;
+// n_hot > 0: LB by k_sssp_relax_hot with that many of them (mode 2 only).
 // Relaxation with the non-atomic filter (byte marks, all zero before and after
 // the pair of calls), then the ordered list of the marked vertices.  With
 // filter, the one-byte distance mirror screens the edges before the key gather;
@@ -656,8 +660,8 @@ hipError_t launch_sssp_relax_marks(int mode, const int32_t* frontier, const int3
                                    int64_t m_f, const int32_t* R, const int32_t* C,
                                    const uint32_t* W, unsigned long long* keys,
                                    const int32_t* perm, uint8_t* marks, DistMirror mirror,
-                                   uint32_t* relaxed, bool filter, const AdvCfg& cfg,
-                                   hipStream_t st);
+                                   uint32_t* relaxed, bool filter, int64_t n_hot, int cu_count,
+                                   const AdvCfg& cfg, hipStream_t st);
 hipError_t launch_sssp_mark_compact(uint8_t* marks, int64_t V, const unsigned long long* keys,
                                     DistMirror mirror, uint32_t* relaxed, int32_t* out_q,
                                     uint32_t* out_count, hipStream_t st);

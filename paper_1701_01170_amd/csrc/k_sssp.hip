@@ -191,6 +191,165 @@ __device__ __forceinline__ uint8_t mirror_of(unsigned long long key, uint32_t sh
   return (uint8_t)(q < kMirrorNone ? q : kMirrorNone);
 }
 
+// The relaxation of SsspMark for large frontiers of long rows in degree-ordered
+// graphs.  What bounds it is the random gather per edge: the L2s fetch a whole
+// 128-byte line for each key they do not hold (R-MAT 22's level of 95 M edges: 22 M
+// such fetches beside 6 M for the edges).  In degree order the first kHotVertices
+// vertices are the ends of most edges (there three quarters, with 3 % of the
+// vertices), so every workgroup keeps their distance mirror in LDS: an edge into one
+// of them gathers its key only if its candidate passes the mirror there, and what it
+// then reads sharpens the entry for the workgroup's later edges.  (The entry stays an
+// upper bound of the distance whatever the order of the byte stores.)  The other
+// edges gather the key, after the global mirror's byte with FILTER, as before.  One
+// workgroup per CU stays for the whole launch, since the table has to be loaded;
+// inside it every wavefront works through chunks of its own (chunk c to wavefront
+// c / workgroups mod their number, so the frontier's order by distance is roughly
+// kept) without barriers: up to 64 frontier segments staged, a long segment's edges
+// with its values in scalar registers, 8 edges in flight per lane.  That level: 1.13
+// ms as k_push_lb<SsspMark<false>>, 0.88 ms here (0.27 ms without its gathers); R-MAT
+// 25's of 731 M edges 8.7 ms and 7.7 ms.
+constexpr int kHotBlock = 1024;
+constexpr int kHotWaves = kHotBlock / kWave;
+
+// Segments with this many edges left are taken by themselves, without a search.
+constexpr uint32_t kHotUniform = 3 * kWave;
+
+template <bool FILTER, int B, class Id>
+__device__ __forceinline__ void hot_commit(const int32_t (&v)[B], const uint32_t (&cand)[B],
+                                           bool (&pass)[B], const Id& id,
+                                           unsigned long long* keys, uint8_t* marks,
+                                           DistMirror mirror, uint8_t* s_hot, int32_t n_hot) {
+  uint32_t m[B];
+#pragma unroll
+  for (int r = 0; r < B; ++r) {
+    m[r] = kMirrorNone;
+    if (v[r] < n_hot) m[r] = s_hot[v[r]];
+    else if (FILTER && pass[r]) m[r] = mirror.p[v[r]];
+  }
+  unsigned long long key[B];
+#pragma unroll
+  for (int r = 0; r < B; ++r) {
+    // ceil(cand / 2^shift) <= m, or no entry
+    const uint32_t q = (cand[r] > 0u ? cand[r] - 1u : 0u) >> mirror.shift;
+    pass[r] = pass[r] && (q < kMirrorNone - 1u ? q : kMirrorNone - 1u) < (cand[r] ? m[r] : 255u);
+    key[r] = pass[r] ? keys[v[r]] : 0ull;
+  }
+#pragma unroll
+  for (int r = 0; r < B; ++r) {
+    if (!pass[r]) continue;
+    const unsigned long long nk = ((unsigned long long)cand[r] << 32) | id(r);
+    if (nk < key[r]) atomicMin(&keys[v[r]], nk);
+    if (cand[r] < (uint32_t)(key[r] >> 32)) marks[v[r]] = 1;
+    if (v[r] < n_hot) {
+      const uint32_t q = mirror_of(nk < key[r] ? nk : key[r], mirror.shift);
+      if (q < m[r]) s_hot[v[r]] = (uint8_t)q;
+    }
+  }
+}
+
+template <bool FILTER>
+__global__ __launch_bounds__(kHotBlock) void k_sssp_relax_hot(
+    const int32_t* __restrict__ frontier, const int32_t* __restrict__ offsets,
+    const int32_t* __restrict__ rstart, const int32_t* __restrict__ chunk_start, int32_t n_f,
+    int32_t m_f, int32_t chunk, const int32_t* __restrict__ C, const uint32_t* __restrict__ W,
+    unsigned long long* __restrict__ keys, uint8_t* __restrict__ marks,
+    const int32_t* __restrict__ perm, DistMirror mirror, uint32_t* __restrict__ relaxed,
+    int32_t n_hot) {
+  constexpr int B = 8;
+  __shared__ uint4 s_hot4[kHotVertices / 16];
+  __shared__ int32_t s_off[kHotWaves][kWave], s_rb[kHotWaves][kWave], s_id[kHotWaves][kWave];
+  __shared__ uint32_t s_du[kHotWaves][kWave];
+  uint8_t* s_hot = reinterpret_cast<uint8_t*>(s_hot4);
+  for (int i = threadIdx.x; i < n_hot / 16; i += kHotBlock)
+    s_hot4[i] = reinterpret_cast<const uint4*>(mirror.p)[i];
+  for (int i = (n_hot & ~15) + (int)threadIdx.x; i < n_hot; i += kHotBlock) s_hot[i] = mirror.p[i];
+  __syncthreads();
+  const int w = threadIdx.x / kWave;
+  const int32_t* off = s_off[w];
+  const int64_t n_chunks = ((int64_t)m_f + chunk - 1) / chunk;
+  for (int64_t c = (int64_t)w * gridDim.x + blockIdx.x; c < n_chunks;
+       c += (int64_t)gridDim.x * kHotWaves) {
+    uint32_t pos = __builtin_amdgcn_readfirstlane((uint32_t)(c * chunk));
+    const uint32_t e1 = (uint32_t)((c + 1) * chunk < m_f ? (c + 1) * chunk : m_f);
+    for (int32_t s = chunk_start[c]; pos < e1; s += kWave) {
+      // stage 64 segments; the first holds edge pos
+      const int32_t i = s + lane();
+      const uint32_t end = (uint32_t)(s + kWave < n_f ? offsets[s + kWave] : m_f);
+      const uint32_t o = i < n_f ? (uint32_t)offsets[i] : (uint32_t)m_f;
+      uint32_t on = __shfl_down(o, 1);
+      if (lane() == kWave - 1) on = end;
+      const uint32_t hi = e1 < end ? e1 : end;
+      if (i < n_f && o < hi && on > pos) {
+        const int32_t u = frontier[i];
+        const uint32_t du = (uint32_t)(keys[u] >> 32);
+        s_rb[w][lane()] = rstart[i];
+        s_du[w][lane()] = du;
+        s_id[w][lane()] = (int32_t)caller_id(perm, u);
+        if (relaxed) atomicMax(&relaxed[u], du + 1u);
+      }
+      s_off[w][lane()] = (int32_t)o;
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      int k0 = 0;
+      for (uint32_t b = pos; b < hi;) {
+        // the segment of edge b, and the edges of it that are left
+        k0 = __builtin_amdgcn_readfirstlane(upper_index(off, k0, kWave - 1, (int64_t)b));
+        const uint32_t send = k0 + 1 < kWave ? __builtin_amdgcn_readfirstlane(off[k0 + 1]) : end;
+        const uint32_t left = (send < hi ? send : hi) - b;
+        if (left >= kHotUniform) {
+          const uint32_t n = left < B * kWave ? left : B * kWave;
+          const int64_t ce = (int64_t)__builtin_amdgcn_readfirstlane(s_rb[w][k0]) +
+                             (b - __builtin_amdgcn_readfirstlane(off[k0]));
+          const uint32_t du = __builtin_amdgcn_readfirstlane(s_du[w][k0]);
+          const uint32_t id = __builtin_amdgcn_readfirstlane(s_id[w][k0]);
+          const int32_t* cp = C + ce;
+          const uint32_t* wp = W + ce;
+          int32_t v[B];
+          uint32_t cand[B];
+          bool pass[B];
+#pragma unroll
+          for (int r = 0; r < B; ++r) {
+            const uint32_t e = r * kWave + lane();
+            pass[r] = e < n;
+            v[r] = pass[r] ? __builtin_nontemporal_load(cp + e) : 0;
+            cand[r] = pass[r] ? __builtin_nontemporal_load(wp + e) : 0u;
+          }
+#pragma unroll
+          for (int r = 0; r < B; ++r) {
+            cand[r] += du;
+            pass[r] = pass[r] && cand[r] >= du && cand[r] != 0xffffffffu;
+          }
+          hot_commit<FILTER, B>(v, cand, pass, [&](int) { return id; }, keys, marks, mirror, s_hot,
+                                n_hot);
+          b += n;
+        } else {
+          int32_t v[B];
+          uint32_t id[B], cand[B];
+          bool pass[B];
+#pragma unroll
+          for (int r = 0; r < B; ++r) {
+            const uint32_t e = b + r * kWave + lane();
+            pass[r] = e < hi;
+            const int k = pass[r] ? upper_index(off, k0, kWave - 1, (int64_t)e) : k0;
+            const int64_t ce = (int64_t)s_rb[w][k] + (e - (uint32_t)off[k]);
+            const uint32_t du = s_du[w][k];
+            v[r] = pass[r] ? C[ce] : 0;
+            cand[r] = du + (pass[r] ? W[ce] : 0u);
+            pass[r] = pass[r] && cand[r] >= du && cand[r] != 0xffffffffu;
+            id[r] = (uint32_t)s_id[w][k];
+          }
+          hot_commit<FILTER, B>(v, cand, pass, [&](int r) { return id[r]; }, keys, marks, mirror,
+                                s_hot, n_hot);
+          b += B * kWave;
+        }
+      }
+      __builtin_amdgcn_wave_barrier();  // the stage is rewritten
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      pos = hi;
+    }
+  }
+}
+
 // Keys of the 32 consecutive vertices v0 .. v0 + 31 (v0 a multiple of 32, all
 // below V), two per 16-byte load.  All loads are issued before any is used:
 // loading only the marked ones (a loop over the set bits, or one branch per
@@ -912,8 +1071,15 @@ hipError_t launch_sssp_relax_marks(int mode, const int32_t* frontier, const int3
                                    int64_t m_f, const int32_t* R, const int32_t* C,
                                    const uint32_t* W, unsigned long long* keys,
                                    const int32_t* perm, uint8_t* marks, const DistMirror mirror,
-                                   uint32_t* relaxed, bool filter, const AdvCfg& cfg,
-                                   hipStream_t st) {
+                                   uint32_t* relaxed, bool filter, int64_t n_hot, int cu_count,
+                                   const AdvCfg& cfg, hipStream_t st) {
+  if (n_hot > 0) {
+    const auto k = filter ? k_sssp_relax_hot<true> : k_sssp_relax_hot<false>;
+    k<<<cu_count, kHotBlock, 0, st>>>(frontier, offsets, rstart, chunk_start, (int32_t)n_f,
+                                      (int32_t)m_f, cfg.chunk, C, W, keys, marks, perm, mirror,
+                                      relaxed, (int32_t)n_hot);
+    return hipGetLastError();
+  }
   if (filter) {
     const SsspMark<true> f{W, keys, marks, perm, mirror, relaxed};
     return push_dispatch(mode, frontier, offsets, rstart, chunk_start, n_f, m_f, R, C, f, nullptr,
