@@ -68,6 +68,7 @@ enum Slot : int {
   S_MIRROR,        // shortest-path one-byte distance mirror [V]
   S_RELAXED,       // shortest-path: 1 + distance a frontier vertex's edges were relaxed with [V]
   S_SSSP_BINS,     // shortest-path distance bins: histograms, cursors, base
+  S_MS_MIRROR,     // batched shortest paths: distance mirror [V * row]
   S_MS_RELAXED,    // batched shortest paths: per (vertex, source) cull values [V * row]
   S_UL_A,          // BFS pull: unvisited vertices with neighbours (two lists, ping-pong)
   S_UL_B,
@@ -387,9 +388,17 @@ hipError_t launch_bc_pull(bool dependency, const int32_t* frontier, const int32_
 hipError_t launch_bc_finalize(const int32_t* depth, const double* sigma, const double* acc,
                               int64_t V, int32_t source, const int32_t* perm, double* bc,
                               double* sigma_out, hipStream_t st);
+// The SSSP distance mirror: one byte per vertex, ceil(dist / 2^shift) of an
+// earlier moment (255: unknown or too large), an upper bound of the distance
+// that screens relaxations before their key gathers.
+struct DistMirror {
+  uint8_t* p;
+  uint32_t shift;
+};
 // batched SSSP (up to 16 sources per pass; see k_msssp.hip): keys per
 // vertex in a row of KS = msssp_row(k) slots; relaxation chunks of
 // msssp_chunk(chunk) edges
+constexpr int64_t kMsScanVertices = 1 << 16;  // graphs up to this size: rotate without next_q
 int msssp_row(int k);
 int msssp_chunk(int chunk);
 // the near / far split: pairs improved to a distance >= T go to fmask and the
@@ -400,34 +409,37 @@ struct MsFar {
   uint32_t* pile_count;
   uint32_t T;
 };
+// mirror (p nullable: no screening; V * KS bytes): a distance mirror per (vertex, source)
+// out_q (relax): candidates of the next frontier; null: not listed (rotate finds them)
 // relaxed (nullable, V * KS words): the per-source cull of pairs already
 // relaxed with their final distance (cleared by init, raised by relax, read
 // and reset by rotate)
 hipError_t launch_msssp_init(unsigned long long* keys, int KS, uint32_t* amask, uint32_t* nmask,
-                             uint32_t* fmask, uint32_t* relaxed, int64_t V, const int32_t* src_dev,
-                             int32_t k, hipStream_t st);
+                             uint32_t* fmask, uint32_t* relaxed, uint8_t* mirror, int64_t V,
+                             const int32_t* src_dev, int32_t k, hipStream_t st);
 hipError_t launch_msssp_relax(int KS, int chunk, const int32_t* frontier, const int32_t* offsets,
                               const int32_t* rstart, const int32_t* chunk_start, int64_t n_f,
                               int64_t m_f, const int32_t* C, const uint32_t* W,
-                              unsigned long long* keys, const uint32_t* amask, uint32_t* nmask,
-                              const MsFar* far, const int32_t* perm, uint32_t* relaxed,
+                              unsigned long long* keys, DistMirror mirror, const uint32_t* amask,
+                              uint32_t* nmask, const MsFar* far, const int32_t* perm, uint32_t* relaxed,
                               int32_t* out_q, uint32_t* out_count, hipStream_t st);
 hipError_t launch_msssp_refill(const int32_t* pile, const uint32_t* n_pile, int64_t max_pile,
                                int32_t* pile_next, uint32_t* n_pile_next,
                                const unsigned long long* keys, int KS, uint32_t* fmask,
                                uint32_t* amask, uint32_t T0, uint32_t T1, int32_t* out_q,
                                uint32_t* out_count, hipStream_t st);
-// amask of the current frontier cleared; the next frontier's vertices get
-// amask = nmask (minus culled pairs), nmask = 0, and those with an active
-// source left are appended to out_q (out_count zero before)
+// amask of the current frontier cleared; the next frontier's vertices (next_q, or
+// null: any of the V, found by their nmask) get amask = nmask (minus culled pairs),
+// nmask = 0, and those with an active source left are appended to out_q (out_count
+// zero before)
 hipError_t launch_msssp_rotate(const int32_t* cur_q, const uint32_t* cur_n, int64_t max_cur,
                                const int32_t* next_q, const uint32_t* next_n, int64_t max_next,
-                               uint32_t* amask, uint32_t* nmask, const unsigned long long* keys,
+                               int64_t V, uint32_t* amask, uint32_t* nmask, const unsigned long long* keys,
                                int KS, uint32_t* relaxed, int32_t* out_q, uint32_t* out_count,
                                hipStream_t st);
 hipError_t launch_msssp_finalize(const unsigned long long* keys, int KS, int32_t k,
                                  const int32_t* R, int64_t V, uint32_t* dist, int32_t* pred,
-                                 const int32_t* perm, const int32_t* src_orig_dev,
+                                 const int32_t* inv, const int32_t* src_orig_dev,
                                  int64_t* reached_edges, hipStream_t st);
 
 // multi-source BFS (64-bit source masks per vertex); depth / parent are the
@@ -614,13 +626,6 @@ hipError_t launch_sssp_pq_dstep(const DlArgs& a, const uint32_t* W, unsigned lon
                                 int32_t* tags, int32_t next_tag, const PqState& pq, bool team,
                                 int n_blocks, hipStream_t st);
 
-// The SSSP distance mirror: one byte per vertex, ceil(dist / 2^shift) of an
-// earlier moment (255: unknown or too large), an upper bound of the distance
-// that screens relaxations before their key gathers.
-struct DistMirror {
-  uint8_t* p;
-  uint32_t shift;
-};
 // quantum 2^shift for a graph whose largest weight is max_weight: 254 steps
 // cover at least four times it
 inline uint32_t mirror_shift_for(uint32_t max_weight) {

@@ -181,4 +181,13 @@ __device__ __forceinline__ T load_shared(const T* p) {
   else return *p;
 }
 
+constexpr uint32_t kMirrorNone = 0xffu;  // a distance mirror's entry: no bound
+
+// mirror entry of a vertex with this key: ceil(dist / 2^shift), or 255
+__device__ __forceinline__ uint8_t mirror_of(unsigned long long key, uint32_t shift) {
+  const uint64_t d = key >> 32;
+  const uint64_t q = (d + ((1ull << shift) - 1ull)) >> shift;
+  return (uint8_t)(q < kMirrorNone ? q : kMirrorNone);
+}
+
 }  // namespace gr

@@ -8,20 +8,22 @@
 //
 // One iteration:
 //   relax  output-balanced like LB: each workgroup takes a chunk of the
-//          frontier's edges and enumerates its (edge, active source) pairs,
-//          consecutive lanes taking the sources of one edge (so their key
-//          gathers share the target's row); a lane relaxes its pair with a
-//          plain read of the target's key and a no-return atomic minimum
-//          (Update_Label), and a lane that lowered the distance ORs its bit
-//          into nmask[v]; the first setter appends v to the next frontier
+//          frontier's edges, a lane an edge.  One load brings the target's row
+//          of one-byte distance bounds (the mirror) and screens all sources of
+//          the edge; the (edge, source) pairs that pass are listed in LDS and
+//          relaxed with a plain read of the target's key and a no-return
+//          atomic minimum (Update_Label).  An edge that lowered distances ORs
+//          their sources into nmask[v] once.  Few edges (LIST): the first
+//          setter appends v to the candidates of the next frontier
 //          (Remove_Redundant for the union);
-//   clear  amask of the current frontier = 0;
-//   move   for the next frontier: amask = nmask, nmask = 0, listing the
-//          vertices with an active source left.
+//   clear  amask of the current frontier = 0 (LIST);
+//   move   for the candidates, or after many edges for every vertex:
+//          amask = nmask, nmask = 0, listing the vertices with an active
+//          source left.
 // With `relaxed` (nullable, KS words per vertex like the keys), each chunk
 // raises relaxed[u][s] to 1 + the distance of (u, s) as it stages u, for every
-// active source s of u (its items read the key after that, so they see that
-// distance or a smaller one), and move resets it when the pair joins the next
+// active source s of u (the distance that the chunk's edges of u are relaxed
+// with), and move resets it when the pair joins the next
 // frontier.  A pair whose relaxed value equals 1 + its distance at move time
 // was active and had every edge relaxed with that final distance, so move
 // drops it (the single-source cull of vertices already relaxed with their
@@ -48,167 +50,216 @@ namespace {
 
 using u64 = unsigned long long;
 
-// Index of the r-th set bit (r < popcount) of a 16-bit mask.
-__device__ __forceinline__ int select_bit(uint32_t m, int r) {
-  int pos = 0;
-#pragma unroll
-  for (int w = 8; w > 0; w >>= 1) {
-    const uint32_t lowm = m & ((1u << w) - 1u);
-    const int c = __popc(lowm);
-    if (r >= c) {
-      r -= c;
-      m >>= w;
-      pos += w;
-    } else {
-      m = lowm;
-    }
-  }
-  return pos;
+// Orders a wavefront's LDS stores before its later loads of them by other lanes.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-template <int N, bool PQ>
+// Appends v of the lanes with `first` to q: one counter atomic per wavefront.
+__device__ __forceinline__ void append_first(bool first, int32_t v, int32_t* __restrict__ q,
+                                             uint32_t* __restrict__ count) {
+  const uint64_t m = __ballot(first);
+  if (!m) return;
+  uint32_t base = 0;
+  if (lane() == 0) base = atomicAdd(count, (uint32_t)__popcll(m));
+  base = __shfl(base, 0);
+  if (first) q[base + (uint32_t)__popcll(m & ((1ull << lane()) - 1ull))] = v;
+}
+
+// A vertex's mirror row: one byte per source.
+template <int KS>
+using MirrorRow = std::conditional_t<KS == 16, uint4, std::conditional_t<KS == 8, uint2, uint32_t>>;
+
+__device__ __forceinline__ uint32_t row_word(const uint4& r, int i) {
+  return i == 0 ? r.x : (i == 1 ? r.y : (i == 2 ? r.z : r.w));
+}
+__device__ __forceinline__ uint32_t row_word(const uint2& r, int i) { return i == 0 ? r.x : r.y; }
+__device__ __forceinline__ uint32_t row_word(uint32_t r, int) { return r; }
+
+constexpr int kMsSegs = 256;   // frontier segments staged per pass
+constexpr int kMsItems = 512;  // listed (edge, source) pairs a wavefront relaxes at a time
+
+// What bounds it: the rows of keys are 128 bytes, one cache line per edge that only
+// the memory behind the L2s holds (R-MAT 20, 16 sources: 134 MB), and the pairs are
+// KS times the edges.  A pair per lane spent some 120 instructions on finding its
+// edge and source and a line per edge on the keys.  Screened with the mirror a pair
+// costs 9 instructions, and an edge 16 bytes of a table an eighth of the size; the
+// mirror is sharpened inside the launch (a byte store per relaxed pair that is lower
+// than the entry; entries stay upper bounds whatever the order of the stores), so
+// that after the first few edges into a vertex only improvements read its keys.
+// The sources' distances of 256 segments are staged in LDS (16 KB, so that 7
+// workgroups share a CU).
+// LIST costs an atomic on one counter per wavefront and 64 edges, some 6.4 ns each:
+// 420 K of them held an iteration of 27 M edges at 2.7 ms.  Without, nmask itself is
+// the list.  R-MAT 20, 16 sources, the four large iterations: 14.3 ms as a pair per
+// lane, 12.0 with LIST, 2.4 without.
+template <int KS, bool PQ, bool LIST>
 __global__ __launch_bounds__(256) void k_msssp_relax(
     const int32_t* __restrict__ frontier, const int32_t* __restrict__ offsets,
     const int32_t* __restrict__ rstart, const int32_t* __restrict__ chunk_start, int32_t n_f,
-    int32_t m_f, const int32_t* __restrict__ C, const uint32_t* __restrict__ W, int KS,
-    u64* __restrict__ keys, const uint32_t* __restrict__ amask, uint32_t* __restrict__ nmask,
-    uint32_t* __restrict__ fmask, int32_t* __restrict__ far_q, uint32_t* __restrict__ far_count,
-    uint32_t T, const int32_t* __restrict__ perm, uint32_t* __restrict__ relaxed,
-    int32_t* __restrict__ out_q, uint32_t* __restrict__ out_count) {
+    int32_t m_f, int32_t chunk, const int32_t* __restrict__ C, const uint32_t* __restrict__ W,
+    u64* __restrict__ keys, DistMirror mirror, const uint32_t* __restrict__ amask,
+    uint32_t* __restrict__ nmask, uint32_t* __restrict__ fmask, int32_t* __restrict__ far_q,
+    uint32_t* __restrict__ far_count, uint32_t T, const int32_t* __restrict__ perm,
+    uint32_t* __restrict__ relaxed, int32_t* __restrict__ out_q,
+    uint32_t* __restrict__ out_count) {
   constexpr int BLOCK = 256;
-  constexpr int CAP = lb_cap(N);
-  constexpr int SPT = (CAP + BLOCK - 1) / BLOCK;  // segments per thread in the item scan
-  constexpr int B = 4;                            // items in flight per lane
-  __shared__ int32_t s_off[CAP + 1];
-  __shared__ int32_t s_u[CAP];
-  __shared__ int32_t s_rb[CAP];
-  __shared__ uint32_t s_am[CAP];
-  __shared__ int32_t s_ioff[CAP + 1];  // first (edge, source) item of each segment in the chunk
-  __shared__ int32_t s_tmp[BLOCK / kWave + 1];
+  constexpr int WAVES = BLOCK / kWave;
+  constexpr int B = 2;  // edges per lane in flight
+  constexpr int J = 2;  // pairs per lane in flight
+  using Row = MirrorRow<KS>;
+  __shared__ int32_t s_off[kMsSegs + 1];
+  __shared__ int32_t s_rb[kMsSegs];
+  __shared__ uint32_t s_id[kMsSegs];
+  __shared__ int32_t s_u[kMsSegs];
+  __shared__ uint16_t s_am[kMsSegs];
+  __shared__ __align__(16) uint32_t s_du[kMsSegs * KS];  // ~0: source not active
+  __shared__ uint16_t s_item[WAVES][kMsItems];           // source << 6 | lane
+  __shared__ uint32_t s_near[WAVES][kWave], s_far[WAVES][kWave];
+  const int wv = threadIdx.x / kWave;
   const int c = blockIdx.x;
-  const int64_t e0 = (int64_t)c * N;
-  const int64_t e1 = e0 + N < m_f ? e0 + N : m_f;
-  const int nchunks = (int)(((int64_t)m_f + N - 1) / N);
+  const int64_t e0 = (int64_t)c * chunk;
+  const int64_t e1 = e0 + chunk < m_f ? e0 + chunk : m_f;
+  const int nchunks = (int)(((int64_t)m_f + chunk - 1) / chunk);
   const int sb = chunk_start[c];
   const int se = c + 1 < nchunks ? chunk_start[c + 1] : n_f - 1;
-  for (int pb = sb; pb <= se; pb += CAP) {
-    const int cnt = (se - pb + 1) < CAP ? (se - pb + 1) : CAP;
+  for (int pb = sb; pb <= se; pb += kMsSegs) {
+    const int cnt = (se - pb + 1) < kMsSegs ? (se - pb + 1) : kMsSegs;
     for (int i = threadIdx.x; i < cnt; i += BLOCK) {
       const int s = pb + i;
-      const int32_t u = frontier[s];
       s_off[i] = offsets[s];
-      s_u[i] = u;
       s_rb[i] = rstart[s];
-      const uint32_t am = amask[u];
-      s_am[i] = am;
-      if (relaxed) {
-        for (uint32_t b = am; b; b &= b - 1) {
-          const int64_t x = (int64_t)u * KS + (__ffs(b) - 1);
-          atomicMax(&relaxed[x], (uint32_t)(keys[x] >> 32) + 1u);
-        }
-      }
+      const int32_t u = frontier[s];
+      s_u[i] = u;
+      s_am[i] = (uint16_t)amask[u];
+      s_id[i] = (uint32_t)(perm ? perm[u] : u);
     }
     if (threadIdx.x == 0) s_off[cnt] = offsets[pb + cnt];
     __syncthreads();
-    // items per segment = (its edges inside [e0, e1)) * (its active sources);
-    // exclusive scan over the segments, SPT consecutive ones per thread
-    int32_t part[SPT];
-    int32_t run = 0;
+    // a thread per (segment, source), so that the rows are read and raised in whole
+    // lines; kRows of them in flight
+    constexpr int kRows = 4;
+    for (int x0 = threadIdx.x; x0 < cnt * KS; x0 += BLOCK * kRows) {
+      uint32_t d[kRows];
 #pragma unroll
-    for (int r = 0; r < SPT; ++r) {
-      const int k = threadIdx.x * SPT + r;
-      int32_t items = 0;
-      if (k < cnt) {
-        const int64_t a = s_off[k] > e0 ? s_off[k] : e0;
-        const int64_t b = s_off[k + 1] < e1 ? s_off[k + 1] : e1;
-        items = b > a ? (int32_t)(b - a) * __popc(s_am[k]) : 0;
+      for (int j = 0; j < kRows; ++j) {
+        const int x = x0 + j * BLOCK;
+        d[j] = ~0u;
+        if (x < cnt * KS && (s_am[x / KS] >> (x % KS) & 1u))
+          d[j] = (uint32_t)(keys[(int64_t)s_u[x / KS] * KS + x % KS] >> 32);
       }
-      part[r] = run;
-      run += items;
-    }
-    int32_t total;
-    const int32_t ex = block_excl_scan<BLOCK>(run, s_tmp, &total);
 #pragma unroll
-    for (int r = 0; r < SPT; ++r) {
-      const int k = threadIdx.x * SPT + r;
-      if (k < cnt) s_ioff[k] = ex + part[r];
+      for (int j = 0; j < kRows; ++j) {
+        const int x = x0 + j * BLOCK;
+        if (x >= cnt * KS) continue;
+        if (relaxed && d[j] != ~0u)
+          atomicMax(&relaxed[(int64_t)s_u[x / KS] * KS + x % KS], d[j] + 1u);
+        s_du[x] = d[j];
+      }
     }
-    if (threadIdx.x == 0) s_ioff[cnt] = total;
     __syncthreads();
-    for (int32_t t0 = 0; t0 < total; t0 += BLOCK * B) {
-      bool ok[B];
-      int32_t u[B], ce[B], src[B], v[B];
+    const int32_t lo = (int32_t)(e0 > s_off[0] ? e0 : s_off[0]);
+    const int32_t hi = (int32_t)(e1 < s_off[cnt] ? e1 : s_off[cnt]);
+    for (int64_t b0 = lo + wv * kWave; b0 < hi; b0 += BLOCK * B) {
+      int32_t v[B], k[B];
       uint32_t w[B];
+      Row row[B];
 #pragma unroll
       for (int r = 0; r < B; ++r) {
-        const int32_t t = t0 + r * BLOCK + threadIdx.x;
-        ok[r] = t < total;
-        int k = 0, sI = 0;
-        int32_t e = 0;
-        if (ok[r]) {
-          k = upper_index(s_ioff, 0, cnt - 1, t);
-          const uint32_t am = s_am[k];
-          const int p = __popc(am);
-          const int32_t j = t - s_ioff[k];
-          const int32_t a = s_off[k] > e0 ? s_off[k] : (int32_t)e0;
-          e = a + j / p;
-          sI = select_bit(am, j % p);
+        const int64_t e = b0 + r * BLOCK + lane();
+        k[r] = -1;
+        v[r] = 0;
+        w[r] = 0;
+        if (e < hi) {
+          k[r] = upper_index(s_off, 0, cnt - 1, e);
+          const int64_t ce = (int64_t)s_rb[k[r]] + (e - s_off[k[r]]);
+          v[r] = C[ce];
+          w[r] = W[ce];
         }
-        u[r] = s_u[k];
-        src[r] = sI;
-        ce[r] = s_rb[k] + (e - s_off[k]);
       }
 #pragma unroll
-      for (int r = 0; r < B; ++r) {
-        v[r] = ok[r] ? C[ce[r]] : 0;
-        w[r] = ok[r] ? W[ce[r]] : 0u;
-      }
-      u64 ku[B], kv[B];
+      for (int r = 0; r < B; ++r)
+        if (mirror.p && k[r] >= 0) row[r] = reinterpret_cast<const Row*>(mirror.p)[v[r]];
 #pragma unroll
       for (int r = 0; r < B; ++r) {
-        ku[r] = ok[r] ? keys[(int64_t)u[r] * KS + src[r]] : 0ull;
-        kv[r] = ok[r] ? keys[(int64_t)v[r] * KS + src[r]] : 0ull;
-      }
-      bool first[B], ffirst[B];
+        // the sources whose candidate may reach or beat the target's distance
+        uint32_t pm = 0;
+        if (k[r] >= 0) {
+          const uint32_t* du = &s_du[k[r] * KS];
 #pragma unroll
-      for (int r = 0; r < B; ++r) {
-        const uint64_t cand = (ku[r] >> 32) + (uint64_t)w[r];
-        first[r] = ffirst[r] = false;
-        if (ok[r] && cand < 0xffffffffull) {
-          const u64 nk = (cand << 32) | (uint32_t)(perm ? perm[u[r]] : u[r]);
-          if (nk < kv[r]) atomicMin(&keys[(int64_t)v[r] * KS + src[r]], nk);
-          if (cand < (kv[r] >> 32)) {
-            const uint32_t bit = 1u << src[r];
-            if (!PQ || cand < (uint64_t)T) first[r] = atomicOr(&nmask[v[r]], bit) == 0u;
-            else ffirst[r] = atomicOr(&fmask[v[r]], bit) == 0u;
+          for (int s = 0; s < KS; ++s) {
+            const uint32_t d = du[s];
+            const uint32_t cand = d + w[r];
+            // ceil(cand / 2^shift) <= the entry, or no entry; no sum past 2^32 - 2
+            const uint32_t q = (cand > 0u ? cand - 1u : 0u) >> mirror.shift;
+            const uint32_t m =
+                mirror.p && cand ? (row_word(row[r], s / 4) >> (8 * (s % 4)) & 0xffu) : kMirrorNone;
+            const bool ok = cand >= d && cand != ~0u &&
+                            (q < kMirrorNone - 1u ? q : kMirrorNone - 1u) < m;
+            pm |= ok ? 1u << s : 0u;
           }
         }
-      }
-      uint32_t n_app = 0, n_far = 0;
+        s_near[wv][lane()] = 0;
+        if constexpr (PQ) s_far[wv][lane()] = 0;
+        const uint32_t n = (uint32_t)__popc(pm);
+        const uint32_t inc = wave_incl_scan(n);
+        const uint32_t total = __builtin_amdgcn_readfirstlane(__shfl(inc, kWave - 1));
+        uint32_t at = inc - n;  // of this lane's next pair
+        for (uint32_t t0 = 0; t0 < total; t0 += kMsItems) {
+          for (; pm && at < t0 + kMsItems; pm &= pm - 1, ++at)
+            s_item[wv][at - t0] = (uint16_t)((__ffs(pm) - 1) << 6 | lane());
+          wave_lds_fence();
+          const uint32_t end = total < t0 + kMsItems ? total : t0 + kMsItems;
+          for (uint32_t t = t0; t < end; t += J * kWave) {
+            u64 key[J], nk[J];
+            int64_t y[J];
+            uint32_t it[J];
 #pragma unroll
-      for (int r = 0; r < B; ++r) {
-        n_app += first[r] ? 1u : 0u;
-        n_far += ffirst[r] ? 1u : 0u;
-      }
-      if (__ballot(n_app != 0)) {
-        const uint32_t inc = wave_incl_scan(n_app);
-        uint32_t base = 0;
-        if (lane() == kWave - 1) base = atomicAdd(out_count, inc);
-        base = __shfl(base, kWave - 1) + inc - n_app;
+            for (int j = 0; j < J; ++j) {
+              const uint32_t x = t + j * kWave + lane();
+              it[j] = x < end ? (uint32_t)s_item[wv][x - t0] : ~0u;
+              const int l = (int)(it[j] & 63u);
+              const int s = (int)(it[j] >> 6) & (KS - 1);
+              const int32_t vl = __shfl(v[r], l);
+              const int32_t kl = __shfl(k[r], l);
+              const uint32_t wl = __shfl(w[r], l);
+              key[j] = 0;
+              if (it[j] != ~0u) {
+                y[j] = (int64_t)vl * KS + s;
+                nk[j] = (u64)(s_du[kl * KS + s] + wl) << 32 | s_id[kl];
+                key[j] = keys[y[j]];
+              }
+            }
 #pragma unroll
-        for (int r = 0; r < B; ++r)
-          if (first[r]) out_q[base++] = v[r];
-      }
-      if constexpr (PQ) {
-        if (__ballot(n_far != 0)) {
-          const uint32_t inc = wave_incl_scan(n_far);
-          uint32_t base = 0;
-          if (lane() == kWave - 1) base = atomicAdd(far_count, inc);
-          base = __shfl(base, kWave - 1) + inc - n_far;
-#pragma unroll
-          for (int r = 0; r < B; ++r)
-            if (ffirst[r]) far_q[base++] = v[r];
+            for (int j = 0; j < J; ++j) {
+              if (it[j] == ~0u) continue;
+              const bool lower = nk[j] < key[j];
+              if (lower) atomicMin(&keys[y[j]], nk[j]);
+              if (mirror.p) {
+                const uint8_t qn = mirror_of(nk[j], mirror.shift);
+                const uint8_t q = lower ? qn : mirror_of(key[j], mirror.shift);
+                if (lower ? q != kMirrorNone : q < qn) mirror.p[y[j]] = q;
+              }
+              if ((uint32_t)(nk[j] >> 32) < (uint32_t)(key[j] >> 32)) {
+                const uint32_t bit = 1u << (it[j] >> 6);
+                if (!PQ || (uint32_t)(nk[j] >> 32) < T) atomicOr(&s_near[wv][it[j] & 63u], bit);
+                else atomicOr(&s_far[wv][it[j] & 63u], bit);
+              }
+            }
+          }
+          wave_lds_fence();  // the list is rewritten
         }
+        if (total == 0) continue;
+        const uint32_t nb = s_near[wv][lane()];
+        if constexpr (LIST)
+          append_first(nb != 0 && atomicOr(&nmask[v[r]], nb) == 0u, v[r], out_q, out_count);
+        else if (nb) atomicOr(&nmask[v[r]], nb);
+        if constexpr (PQ) {
+          const uint32_t fb = s_far[wv][lane()];
+          append_first(fb != 0 && atomicOr(&fmask[v[r]], fb) == 0u, v[r], far_q, far_count);
+        }
+        wave_lds_fence();
       }
     }
     __syncthreads();
@@ -249,18 +300,20 @@ __global__ __launch_bounds__(256) void k_msssp_refill(
   }
 }
 
-// keys = no path (~0), masks = 0, then the sources: key (0, -1) and the
+// keys = no path (~0), mirror = no entry, masks = 0, then the sources: key (0, -1) and the
 // source's bit in amask; the distinct source vertices form frontier 0.
 __global__ __launch_bounds__(256) void k_msssp_init(u64* __restrict__ keys, int KS,
                                                     uint32_t* __restrict__ amask,
                                                     uint32_t* __restrict__ nmask,
                                                     uint32_t* __restrict__ fmask,
-                                                    uint32_t* __restrict__ relaxed, int64_t V) {
+                                                    uint32_t* __restrict__ relaxed,
+                                                    uint8_t* __restrict__ mirror, int64_t V) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t n = V * KS;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
     keys[i] = ~0ull;
     if (relaxed) relaxed[i] = 0u;
+    if (mirror && i < n / 4) reinterpret_cast<uint32_t*>(mirror)[i] = ~0u;
     if (i < V) {
       amask[i] = 0u;
       nmask[i] = 0u;
@@ -287,56 +340,116 @@ __global__ __launch_bounds__(256) void k_msssp_clear(const int32_t* __restrict__
   if (i < (int64_t)*n) amask[q[i]] = 0u;
 }
 
-// Every workgroup thread calls block_append once, so no early return.
+// LIST: over the *n vertices of q; otherwise over all V, which also clears amask.
+// KS lanes per vertex, so that the rows are read in whole lines, four rows in flight
+// per lane.  The appends share one counter (6.4 ns each): many vertices go in tiles
+// of 1024, a list or a small graph, which need workgroups more than fewer appends, in
+// tiles of 64 (16 K vertices: 15 us in tiles of 1024, 5 in tiles of 64).
+template <int KS, bool LIST, int kMoveTile>
 __global__ __launch_bounds__(256) void k_msssp_move(const int32_t* __restrict__ q,
-                                                    const uint32_t* __restrict__ n,
+                                                    const uint32_t* __restrict__ n, int64_t V,
                                                     uint32_t* __restrict__ amask,
                                                     uint32_t* __restrict__ nmask,
-                                                    const u64* __restrict__ keys, int KS,
+                                                    const u64* __restrict__ keys,
                                                     uint32_t* __restrict__ relaxed,
                                                     int32_t* __restrict__ out_q,
                                                     uint32_t* __restrict__ out_count) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int32_t v = 0;
-  uint32_t nm = 0;
-  if (i < (int64_t)*n) {
-    v = q[i];
-    nm = nmask[v];
-    nmask[v] = 0u;
-    if (relaxed) {
-      for (uint32_t b = nm; b; b &= b - 1) {
-        const int sI = __ffs(b) - 1;
-        const int64_t x = (int64_t)v * KS + sI;
-        const uint32_t r = relaxed[x];
-        if (r == (uint32_t)(keys[x] >> 32) + 1u) nm &= ~(1u << sI);
-        else if (r) relaxed[x] = 0u;
+  constexpr int VPT = (kMoveTile + 255) / 256;
+  constexpr int STEP = 256 / KS;                // vertices per turn
+  constexpr int U = kMoveTile / STEP < 4 ? 1 : 4;
+  static_assert(kMoveTile % (STEP * U) == 0);
+  __shared__ int32_t s_v[kMoveTile];
+  __shared__ uint16_t s_nm[kMoveTile];
+  const int64_t count = LIST ? (int64_t)*n : V;
+  const int sI = threadIdx.x % KS;
+  for (int64_t b0 = (int64_t)blockIdx.x * kMoveTile; b0 < count;
+       b0 += (int64_t)gridDim.x * kMoveTile) {
+#pragma unroll
+    for (int r = 0; r < VPT; ++r) {
+      const int j = r * 256 + threadIdx.x;
+      if (j >= kMoveTile) continue;
+      int32_t v = 0;
+      uint32_t nm = 0;
+      if (b0 + j < count) {
+        v = LIST ? q[b0 + j] : (int32_t)(b0 + j);
+        nm = nmask[v];
       }
+      s_v[j] = v;
+      s_nm[j] = (uint16_t)nm;
     }
-    amask[v] = nm;
+    __syncthreads();
+    if (relaxed) {
+      for (int j0 = threadIdx.x / KS; j0 < kMoveTile; j0 += STEP * U) {
+        bool on[U];
+        uint32_t rel[U], d[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          const int64_t x = (int64_t)s_v[j0 + j * STEP] * KS + sI;
+          on[j] = s_nm[j0 + j * STEP] >> sI & 1u;
+          rel[j] = on[j] ? relaxed[x] : 0u;
+          d[j] = on[j] ? (uint32_t)(keys[x] >> 32) : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+          if (on[j] && rel[j] == d[j] + 1u) on[j] = false;
+          else if (rel[j]) relaxed[(int64_t)s_v[j0 + j * STEP] * KS + sI] = 0u;
+          const uint32_t nm = (uint32_t)(__ballot(on[j]) >> (lane() - sI)) & ((1u << KS) - 1u);
+          if (sI == 0) s_nm[j0 + j * STEP] = (uint16_t)nm;
+        }
+      }
+      __syncthreads();
+    }
+    uint32_t listed = 0;
+#pragma unroll
+    for (int r = 0; r < VPT; ++r) {
+      const int j = r * 256 + threadIdx.x;
+      if (j >= kMoveTile || b0 + j >= count) continue;
+      nmask[s_v[j]] = 0u;
+      amask[s_v[j]] = s_nm[j];
+      listed += s_nm[j] ? 1u : 0u;
+    }
+    uint32_t a = block_append<256>(listed, out_count);
+#pragma unroll
+    for (int r = 0; r < VPT; ++r) {
+      const int j = r * 256 + threadIdx.x;
+      if (j < kMoveTile && b0 + j < count && s_nm[j]) out_q[a++] = s_v[j];
+    }
+    __syncthreads();  // the tile is rewritten
   }
-  const uint32_t a = block_append<256>(nm ? 1u : 0u, out_count);
-  if (nm) out_q[a] = v;
 }
 
-// dist[s][v] / pred[s][v] at caller ids for the k sources of the pass, and the
-// sum over sources of the degrees of their reached vertices.
-__global__ __launch_bounds__(256) void k_msssp_finalize(const u64* __restrict__ keys, int KS,
-                                                        int32_t k, const int32_t* __restrict__ R,
+// dist[s][o] / pred[s][o] at caller ids for the k sources of the pass, and the sum
+// over sources of the degrees of their reached vertices (R: the caller's row
+// offsets).  Threads run over caller ids: a row of keys is read wherever it lies as
+// whole lines, and the outputs are written in order (the other way round, each of 32
+// arrays is written 4 bytes at a time: 383 us, now 54, for R-MAT 20 and 16 sources).
+template <int KS>
+__global__ __launch_bounds__(256) void k_msssp_finalize(const u64* __restrict__ keys, int32_t k,
+                                                        const int32_t* __restrict__ R,
                                                         int64_t V, uint32_t* __restrict__ dist,
                                                         int32_t* __restrict__ pred,
-                                                        const int32_t* __restrict__ perm,
+                                                        const int32_t* __restrict__ inv,
                                                         int64_t* __restrict__ reached_edges) {
   __shared__ int64_t s[256 / kWave];
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   int64_t acc = 0;
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += stride) {
-    const int64_t o = perm ? perm[v] : v;
-    const int64_t deg = (int64_t)R[v + 1] - R[v];
-    for (int sI = 0; sI < k; ++sI) {
-      const u64 key = keys[v * KS + sI];
-      const uint32_t d = (uint32_t)(key >> 32);
+  for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < V; o += stride) {
+    const int64_t v = inv ? inv[o] : o;
+    const int64_t deg = (int64_t)R[o + 1] - R[o];
+    u64 key[KS];
+    const ulonglong2* row = reinterpret_cast<const ulonglong2*>(keys + v * KS);
+#pragma unroll
+    for (int j = 0; j < KS / 2; ++j) {
+      const ulonglong2 x = row[j];
+      key[2 * j] = x.x;
+      key[2 * j + 1] = x.y;
+    }
+#pragma unroll
+    for (int sI = 0; sI < KS; ++sI) {
+      if (sI >= k) break;
+      const uint32_t d = (uint32_t)(key[sI] >> 32);
       dist[(int64_t)sI * V + o] = d;
-      if (pred) pred[(int64_t)sI * V + o] = (int32_t)(uint32_t)(key & 0xffffffffull);
+      if (pred) pred[(int64_t)sI * V + o] = (int32_t)(uint32_t)(key[sI] & 0xffffffffull);
       if (d != 0xffffffffu) acc += deg;
     }
   }
@@ -361,24 +474,6 @@ __global__ __launch_bounds__(64) void k_msssp_source_pred(const int32_t* __restr
 
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
-template <bool PQ>
-hipError_t relax_n(int chunk, unsigned g, const int32_t* frontier, const int32_t* offsets,
-                   const int32_t* rstart, const int32_t* chunk_start, int32_t n_f, int32_t m_f,
-                   const int32_t* C, const uint32_t* W, int KS, u64* keys, const uint32_t* amask,
-                   uint32_t* nmask, uint32_t* fmask, int32_t* far_q, uint32_t* far_count,
-                   uint32_t T, const int32_t* perm, uint32_t* relaxed, int32_t* out_q,
-                   uint32_t* out_count, hipStream_t st) {
-#define GR_MS_RELAX(CH)                                                                        \
-  k_msssp_relax<CH, PQ><<<g, 256, 0, st>>>(frontier, offsets, rstart, chunk_start, n_f, m_f, C, \
-                                           W, KS, keys, amask, nmask, fmask, far_q, far_count,   \
-                                           T, perm, relaxed, out_q, out_count)
-  if (chunk == 512) GR_MS_RELAX(512);
-  else if (chunk == 2048) GR_MS_RELAX(2048);
-  else GR_MS_RELAX(1024);
-#undef GR_MS_RELAX
-  return hipGetLastError();
-}
-
 }  // namespace
 
 int msssp_row(int k) { return k <= 4 ? 4 : (k <= 8 ? 8 : 16); }
@@ -386,31 +481,45 @@ int msssp_row(int k) { return k <= 4 ? 4 : (k <= 8 ? 8 : 16); }
 int msssp_chunk(int chunk) { return chunk == 512 || chunk == 2048 ? chunk : 1024; }
 
 hipError_t launch_msssp_init(u64* keys, int KS, uint32_t* amask, uint32_t* nmask, uint32_t* fmask,
-                             uint32_t* relaxed, int64_t V, const int32_t* src_dev, int32_t k,
-                             hipStream_t st) {
+                             uint32_t* relaxed, uint8_t* mirror, int64_t V,
+                             const int32_t* src_dev, int32_t k, hipStream_t st) {
   int64_t g = blocks_for(V * KS, 256);
   if (g > 8192) g = 8192;
-  k_msssp_init<<<(unsigned)g, 256, 0, st>>>(keys, KS, amask, nmask, fmask, relaxed, V);
+  k_msssp_init<<<(unsigned)g, 256, 0, st>>>(keys, KS, amask, nmask, fmask, relaxed, mirror,
+                                            V);
   k_msssp_seed<<<1, 64, 0, st>>>(src_dev, k, KS, keys, amask);
   return hipGetLastError();
 }
 
+#define GR_MS_ROW(KS, CALL)          \
+  switch (KS) {                       \
+    case 4: { constexpr int R_ = 4; CALL; break; }   \
+    case 8: { constexpr int R_ = 8; CALL; break; }   \
+    default: { constexpr int R_ = 16; CALL; break; } \
+  }
+
 hipError_t launch_msssp_relax(int KS, int chunk, const int32_t* frontier, const int32_t* offsets,
                               const int32_t* rstart, const int32_t* chunk_start, int64_t n_f,
                               int64_t m_f, const int32_t* C, const uint32_t* W, u64* keys,
-                              const uint32_t* amask, uint32_t* nmask, const MsFar* far,
-                              const int32_t* perm, uint32_t* relaxed, int32_t* out_q,
-                              uint32_t* out_count, hipStream_t st) {
+                              DistMirror mirror, const uint32_t* amask, uint32_t* nmask,
+                              const MsFar* far, const int32_t* perm, uint32_t* relaxed,
+                              int32_t* out_q, uint32_t* out_count, hipStream_t st) {
   if (n_f <= 0 || m_f <= 0) return hipSuccess;
-  const int ch = msssp_chunk(chunk);
-  const unsigned g = blocks_for(m_f, ch);
-  if (far)
-    return relax_n<true>(ch, g, frontier, offsets, rstart, chunk_start, (int32_t)n_f, (int32_t)m_f,
-                         C, W, KS, keys, amask, nmask, far->fmask, far->pile, far->pile_count,
-                         far->T, perm, relaxed, out_q, out_count, st);
-  return relax_n<false>(ch, g, frontier, offsets, rstart, chunk_start, (int32_t)n_f, (int32_t)m_f,
-                        C, W, KS, keys, amask, nmask, nullptr, nullptr, nullptr, 0u, perm, relaxed,
-                        out_q, out_count, st);
+  const unsigned g = blocks_for(m_f, chunk);
+#define GR_MS_RELAX(FAR, LIST, FM, FQ, FN, FT)                                              \
+  GR_MS_ROW(KS, (k_msssp_relax<R_, FAR, LIST><<<g, 256, 0, st>>>(                           \
+                    frontier, offsets, rstart, chunk_start, (int32_t)n_f, (int32_t)m_f,     \
+                    chunk, C, W, keys, mirror, amask, nmask, FM, FQ, FN, FT, perm, relaxed, \
+                    out_q, out_count)))
+  if (far) {
+    if (out_q) GR_MS_RELAX(true, true, far->fmask, far->pile, far->pile_count, far->T)
+    else GR_MS_RELAX(true, false, far->fmask, far->pile, far->pile_count, far->T)
+  } else {
+    if (out_q) GR_MS_RELAX(false, true, nullptr, nullptr, nullptr, 0u)
+    else GR_MS_RELAX(false, false, nullptr, nullptr, nullptr, 0u)
+  }
+#undef GR_MS_RELAX
+  return hipGetLastError();
 }
 
 hipError_t launch_msssp_refill(const int32_t* pile, const uint32_t* n_pile, int64_t max_pile,
@@ -427,23 +536,34 @@ hipError_t launch_msssp_refill(const int32_t* pile, const uint32_t* n_pile, int6
 
 hipError_t launch_msssp_rotate(const int32_t* cur_q, const uint32_t* cur_n, int64_t max_cur,
                                const int32_t* next_q, const uint32_t* next_n, int64_t max_next,
-                               uint32_t* amask, uint32_t* nmask, const u64* keys, int KS,
+                               int64_t V, uint32_t* amask, uint32_t* nmask, const u64* keys, int KS,
                                uint32_t* relaxed, int32_t* out_q, uint32_t* out_count,
                                hipStream_t st) {
-  if (max_cur > 0) k_msssp_clear<<<blocks_for(max_cur, 256), 256, 0, st>>>(cur_q, cur_n, amask);
-  if (max_next > 0)
-    k_msssp_move<<<blocks_for(max_next, 256), 256, 0, st>>>(next_q, next_n, amask, nmask, keys, KS,
-                                                            relaxed, out_q, out_count);
+  if (next_q && max_cur > 0)
+    k_msssp_clear<<<blocks_for(max_cur, 256), 256, 0, st>>>(cur_q, cur_n, amask);
+  const int64_t n = next_q ? max_next : V;
+  if (n <= 0) return hipGetLastError();
+  const bool large = !next_q && n > kMsScanVertices;
+  unsigned g = blocks_for(n, large ? 1024 : 64);
+  if (g > 4096) g = 4096;
+#define GR_MS_MOVE(LIST, TILE)                                                                  \
+  GR_MS_ROW(KS, (k_msssp_move<R_, LIST, TILE><<<g, 256, 0, st>>>(next_q, next_n, V, amask, nmask, \
+                                                                 keys, relaxed, out_q, out_count)))
+  if (next_q) GR_MS_MOVE(true, 64)
+  else if (large) GR_MS_MOVE(false, 1024)
+  else GR_MS_MOVE(false, 64)
+#undef GR_MS_MOVE
   return hipGetLastError();
 }
 
 hipError_t launch_msssp_finalize(const u64* keys, int KS, int32_t k, const int32_t* R, int64_t V,
-                                 uint32_t* dist, int32_t* pred, const int32_t* perm,
+                                 uint32_t* dist, int32_t* pred, const int32_t* inv,
                                  const int32_t* src_orig_dev, int64_t* reached_edges,
                                  hipStream_t st) {
   unsigned g = blocks_for(V, 256);
-  if (g > 1024) g = 1024;
-  k_msssp_finalize<<<g, 256, 0, st>>>(keys, KS, k, R, V, dist, pred, perm, reached_edges);
+  if (g > 2048) g = 2048;
+  GR_MS_ROW(KS, (k_msssp_finalize<R_><<<g, 256, 0, st>>>(keys, k, R, V, dist, pred, inv,
+                                                         reached_edges)))
   if (pred) k_msssp_source_pred<<<1, 64, 0, st>>>(src_orig_dev, k, V, pred);
   return hipGetLastError();
 }

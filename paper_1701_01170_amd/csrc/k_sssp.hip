@@ -125,8 +125,6 @@ struct SsspVisit {
 // work already done).  A value left from an earlier iteration is larger than
 // 1 + any distance v can have after dropping in this one, and 0 never
 // matches, so nothing else is dropped.
-constexpr uint32_t kMirrorNone = 0xffu;
-
 template <bool FILTER>
 struct SsspMark {
   const uint32_t* __restrict__ W;
@@ -183,13 +181,6 @@ struct SsspMark {
   }
   __device__ __forceinline__ bool commit(int32_t, int32_t, int32_t, uint32_t) const { return false; }
 };
-
-// mirror entry of a vertex with this key: ceil(dist / 2^shift), or 255
-__device__ __forceinline__ uint8_t mirror_of(unsigned long long key, uint32_t shift) {
-  const uint64_t d = key >> 32;
-  const uint64_t q = (d + ((1ull << shift) - 1ull)) >> shift;
-  return (uint8_t)(q < kMirrorNone ? q : kMirrorNone);
-}
 
 // The relaxation of SsspMark for large frontiers of long rows in degree-ordered
 // graphs.  What bounds it is the random gather per edge: the L2s fetch a whole
