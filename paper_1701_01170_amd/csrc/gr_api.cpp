@@ -1349,7 +1349,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
     GR_TRY(pool_typed(ctx, S_FAR_TAGS, V, &pq.far_tag));
   }
   // distance bins of the marks compaction
-  SsspBins bins{nullptr, 0u};
+  SsspBins bins{nullptr, 0u, 0};
   if (!use_pq && !(opts.sssp_opt_off & GR_SSSP_OPT_BINS)) {
     GR_TRY(pool_typed(ctx, S_SSSP_BINS, kSsspBinWords, &bins.state));
     bins.shift = bin_shift_for(g->max_weight);
@@ -1558,10 +1558,11 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
         if (use_pq)
           GR_HIP(launch_sssp_pq_mark_compact(marks, V, keys, mirror, relaxed, pq, ctrl,
                                              q[(cur + 1) % 3], &ctrl->q_count[(cur + 1) % 3], st));
-        else if (bins.state)
+        else if (bins.state) {
           GR_HIP(launch_sssp_bin_compact(marks, V, keys, mirror, relaxed, bins, q[(cur + 1) % 3],
                                          &ctrl->q_count[(cur + 1) % 3], st));
-        else
+          bins.set ^= 1;
+        } else
           GR_HIP(launch_sssp_mark_compact(marks, V, keys, mirror, relaxed, q[(cur + 1) % 3],
                                           &ctrl->q_count[(cur + 1) % 3], st));
       } else if (use_pq) {

@@ -674,13 +674,15 @@ hipError_t launch_sssp_mark_compact(uint8_t* marks, int64_t V, const unsigned lo
 // listed in bins of distance, smallest first; *out_count is set, not added to.
 constexpr int kSsspBins = 128;
 constexpr int kBinCopies = 8;
-constexpr int kSsspBinHist = 0;                                 // [kBinCopies][kSsspBins]
-constexpr int kSsspBinCursor = kBinCopies * kSsspBins;          // [kBinCopies][kSsspBins]
-constexpr int kSsspBinBase = 2 * kBinCopies * kSsspBins;        // lower bound of the distances
-constexpr int kSsspBinWords = 2 * kBinCopies * kSsspBins + 1;
+constexpr int kSsspBinHist = 0;                           // [kBinCopies][kSsspBins]
+constexpr int kSsspBinCursor = kBinCopies * kSsspBins;    // [kBinCopies][kSsspBins]
+constexpr int kSsspBinBase = 2 * kBinCopies * kSsspBins;  // lower bound of the distances
+constexpr int kSsspBinSet = 2 * kBinCopies * kSsspBins + 1;
+constexpr int kSsspBinWords = 2 * kSsspBinSet;            // two sets, used in turn
 struct SsspBins {
   uint32_t* state;  // kSsspBinWords words
   uint32_t shift;   // bin width 2^shift
+  int set;          // 0 or 1: the set of this call; the next call takes the other
 };
 hipError_t launch_sssp_bin_compact(uint8_t* marks, int64_t V, const unsigned long long* keys,
                                    DistMirror mirror, uint32_t* relaxed, const SsspBins& bins,

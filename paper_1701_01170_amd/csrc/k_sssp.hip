@@ -434,27 +434,30 @@ __global__ __launch_bounds__(256) void k_sssp_mark_compact(uint8_t* __restrict__
 // non-empty bin (distances assigned in an iteration are at least the
 // smallest distance of its frontier).  Pass 1 culls, refreshes the mirror,
 // writes bin + 1 into the mark byte and counts bins per workgroup into one of
-// kBinCopies histograms; the scan lays the bins out (copies of a bin in
-// order) and moves base; pass 2, on the same grid, scatters each vertex into
-// its bin's range (order inside a bin: by workgroup, then arbitrary).
-__device__ __forceinline__ uint32_t peek_marks(const uint8_t* __restrict__ marks, int64_t w,
-                                               int64_t V, uint8_t (&m)[32]) {
-  const int64_t v0 = w * 32;
+// kBinCopies histograms; pass 2, on the same grid, lays the bins out (every workgroup
+// for itself, from the histograms: a kernel for it took 4.3 us and a boundary) and
+// scatters each vertex into its bin's range (copies of a bin in order, order inside a
+// copy arbitrary).  Its first workgroup moves base and clears the other of two sets of
+// histograms and cursors, which the next binned iteration uses.  kBinItems vertices
+// per thread: at 32 a graph of 300 K vertices gave work to 37 workgroups, whose loads
+// held pass 1 at 11.3 us (4.9 at 8) and pass 2 at 6.1 (5.3 with the layout).
+constexpr int kBinItems = 8;
+
+// Marks of the kBinItems vertices from v0 (a multiple of kBinItems).
+__device__ __forceinline__ uint32_t peek_marks(const uint8_t* __restrict__ marks, int64_t v0,
+                                               int64_t V, uint8_t (&m)[kBinItems]) {
   uint32_t mask = 0;
-  if (v0 + 32 <= V) {
-    const uint4* m4 = reinterpret_cast<const uint4*>(marks + v0);
-    const uint4 a = m4[0], b = m4[1];
-    const uint32_t q[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  if (v0 + kBinItems <= V) {
+    const uint2 a = *reinterpret_cast<const uint2*>(marks + v0);
+    const uint32_t q[2] = {a.x, a.y};
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        m[4 * i + k] = (uint8_t)(q[i] >> (8 * k));
-        if (m[4 * i + k]) mask |= 1u << (4 * i + k);
-      }
+    for (int b = 0; b < kBinItems; ++b) {
+      m[b] = (uint8_t)(q[b / 4] >> (8 * (b % 4)));
+      if (m[b]) mask |= 1u << b;
+    }
   } else {
 #pragma unroll
-    for (int b = 0; b < 32; ++b) {
+    for (int b = 0; b < kBinItems; ++b) {
       m[b] = v0 + b < V ? marks[v0 + b] : (uint8_t)0;
       if (m[b]) mask |= 1u << b;
     }
@@ -462,20 +465,17 @@ __device__ __forceinline__ uint32_t peek_marks(const uint8_t* __restrict__ marks
   return mask;
 }
 
-__device__ __forceinline__ void put_marks(uint8_t* __restrict__ marks, int64_t w, int64_t V,
-                                          const uint8_t (&m)[32]) {
-  const int64_t v0 = w * 32;
-  if (v0 + 32 <= V) {
-    uint32_t q[8];
+__device__ __forceinline__ void put_marks(uint8_t* __restrict__ marks, int64_t v0, int64_t V,
+                                          const uint8_t (&m)[kBinItems]) {
+  if (v0 + kBinItems <= V) {
+    uint32_t q[2];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 2; ++i)
       q[i] = (uint32_t)m[4 * i] | ((uint32_t)m[4 * i + 1] << 8) | ((uint32_t)m[4 * i + 2] << 16) |
              ((uint32_t)m[4 * i + 3] << 24);
-    uint4* z = reinterpret_cast<uint4*>(marks + v0);
-    z[0] = make_uint4(q[0], q[1], q[2], q[3]);
-    z[1] = make_uint4(q[4], q[5], q[6], q[7]);
+    *reinterpret_cast<uint2*>(marks + v0) = make_uint2(q[0], q[1]);
   } else {
-    for (int b = 0; b < 32 && v0 + b < V; ++b) marks[v0 + b] = m[b];
+    for (int b = 0; b < kBinItems && v0 + b < V; ++b) marks[v0 + b] = m[b];
   }
 }
 
@@ -492,27 +492,42 @@ __global__ __launch_bounds__(256) void k_sssp_bin_count(uint8_t* __restrict__ ma
   __shared__ uint32_t s_h[kSsspBins];
   for (int i = threadIdx.x; i < kSsspBins; i += 256) s_h[i] = 0;
   __syncthreads();
-  const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const uint32_t base = bins.state[kSsspBinBase];
-  uint8_t m[32];
-  const uint32_t mask = w < (V + 31) / 32 ? peek_marks(marks, w, V, m) : 0u;
+  const int64_t v0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * kBinItems;
+  uint32_t* set = bins.state + bins.set * kSsspBinSet;
+  const uint32_t base = set[kSsspBinBase];
+  uint8_t m[kBinItems];
+  const uint32_t mask = v0 < V ? peek_marks(marks, v0, V, m) : 0u;
   if (mask) {
-    const int64_t v0 = w * 32;
-    unsigned long long k[32];
-    uint32_t r[32];
-    if (v0 + 32 <= V) {
-      word_keys(keys, v0, k);
-      if (relaxed) word_relaxed(relaxed, v0, r);
+    unsigned long long k[kBinItems];
+    uint32_t r[kBinItems];
+    if (v0 + kBinItems <= V) {
+      // all loads are issued before any is used (see word_keys)
+      const ulonglong2* __restrict__ k2 = reinterpret_cast<const ulonglong2*>(keys + v0);
+      const uint4* __restrict__ r4 = reinterpret_cast<const uint4*>(relaxed + v0);
+#pragma unroll
+      for (int j = 0; j < kBinItems / 2; ++j) {
+        const ulonglong2 x = k2[j];
+        k[2 * j] = x.x;
+        k[2 * j + 1] = x.y;
+      }
+#pragma unroll
+      for (int j = 0; j < kBinItems / 4; ++j) {
+        const uint4 x = relaxed ? r4[j] : make_uint4(0u, 0u, 0u, 0u);
+        r[4 * j] = x.x;
+        r[4 * j + 1] = x.y;
+        r[4 * j + 2] = x.z;
+        r[4 * j + 3] = x.w;
+      }
     } else {
 #pragma unroll
-      for (int b = 0; b < 32; ++b) {
+      for (int b = 0; b < kBinItems; ++b) {
         const bool in = (mask >> b) & 1u;
         k[b] = in ? keys[v0 + b] : 0ull;
         r[b] = in && relaxed ? relaxed[v0 + b] : 0u;
       }
     }
 #pragma unroll
-    for (int b = 0; b < 32; ++b) {
+    for (int b = 0; b < kBinItems; ++b) {
       if (!((mask >> b) & 1u)) continue;
       mirror.p[v0 + b] = mirror_of(k[b], mirror.shift);
       if (relaxed && drop_relaxed(relaxed, v0 + b, k[b], r[b])) {
@@ -523,78 +538,78 @@ __global__ __launch_bounds__(256) void k_sssp_bin_count(uint8_t* __restrict__ ma
       m[b] = (uint8_t)(bin + 1u);
       atomicAdd(&s_h[bin], 1u);
     }
-    put_marks(marks, w, V, m);
+    put_marks(marks, v0, V, m);
   }
   __syncthreads();
-  uint32_t* h = bins.state + kSsspBinHist + (blockIdx.x % kBinCopies) * kSsspBins;
+  uint32_t* h = set + kSsspBinHist + (blockIdx.x % kBinCopies) * kSsspBins;
   for (int i = threadIdx.x; i < kSsspBins; i += 256)
     if (s_h[i]) atomicAdd(&h[i], s_h[i]);
 }
 
-// One workgroup of kSsspBins threads: bin ranges (cursor of copy c of bin b =
-// start of bin b + the counts of copies before c), the histograms cleared,
-// the next base, and the frontier size.
-__global__ __launch_bounds__(kSsspBins) void k_sssp_bin_scan(SsspBins bins,
-                                                             uint32_t* __restrict__ out_count) {
-  __shared__ uint32_t s_tmp[kSsspBins / kWave];
-  __shared__ uint32_t s_first;
-  const int b = threadIdx.x;
-  uint32_t* h = bins.state + kSsspBinHist;
-  uint32_t* cur = bins.state + kSsspBinCursor;
-  uint32_t c[kBinCopies];
-  uint32_t tot = 0;
-#pragma unroll
-  for (int i = 0; i < kBinCopies; ++i) {
-    c[i] = h[i * kSsspBins + b];
-    tot += c[i];
-  }
-  if (b == 0) s_first = kSsspBins;
-  const uint32_t inc = wave_incl_scan(tot);
-  if (lane() == kWave - 1) s_tmp[b / kWave] = inc;
-  __syncthreads();
-  if (tot) atomicMin(&s_first, (uint32_t)b);
-  uint32_t start = inc - tot;
-  for (int i = 0; i < b / kWave; ++i) start += s_tmp[i];
-#pragma unroll
-  for (int i = 0; i < kBinCopies; ++i) {
-    cur[i * kSsspBins + b] = start;
-    start += c[i];
-    h[i * kSsspBins + b] = 0u;
-  }
-  __syncthreads();
-  if (b == kSsspBins - 1) {
-    *out_count = start;
-    const uint32_t f = s_first;
-    if (f < (uint32_t)kSsspBins) bins.state[kSsspBinBase] += f << bins.shift;
-  }
-}
-
 __global__ __launch_bounds__(256) void k_sssp_bin_scatter(uint8_t* __restrict__ marks, int64_t V,
                                                           SsspBins bins,
-                                                          int32_t* __restrict__ out_q) {
+                                                          int32_t* __restrict__ out_q,
+                                                          uint32_t* __restrict__ out_count) {
   __shared__ uint32_t s_n[kSsspBins];
-  for (int i = threadIdx.x; i < kSsspBins; i += 256) s_n[i] = 0;
+  __shared__ uint32_t s_tmp[kSsspBins / kWave];
+  __shared__ uint32_t s_first;
+  static_assert(kSsspBins <= 256 && kSsspBins % kWave == 0);
+  const int t = threadIdx.x;
+  const bool is_bin = t < kSsspBins;
+  if (is_bin) s_n[t] = 0;
+  if (t == 0) s_first = kSsspBins;
   __syncthreads();
-  const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  uint8_t m[32];
-  const uint32_t mask = w < (V + 31) / 32 ? peek_marks(marks, w, V, m) : 0u;
-  uint32_t rank[32];
+  uint32_t* set = bins.state + bins.set * kSsspBinSet;
+  const int copy = blockIdx.x % kBinCopies;
+  // this copy's start in the thread's bin, but for the bins before
+  uint32_t start = 0, tot = 0;
+  if (is_bin) {
 #pragma unroll
-  for (int b = 0; b < 32; ++b) rank[b] = (mask >> b) & 1u ? atomicAdd(&s_n[m[b] - 1], 1u) : 0u;
+    for (int i = 0; i < kBinCopies; ++i) {
+      const uint32_t c = set[kSsspBinHist + i * kSsspBins + t];
+      start += i < copy ? c : 0u;
+      tot += c;
+    }
+  }
+  const int64_t v0 = ((int64_t)blockIdx.x * 256 + t) * kBinItems;
+  uint8_t m[kBinItems];
+  const uint32_t mask = v0 < V ? peek_marks(marks, v0, V, m) : 0u;
+  uint32_t rank[kBinItems];
+#pragma unroll
+  for (int b = 0; b < kBinItems; ++b)
+    rank[b] = (mask >> b) & 1u ? atomicAdd(&s_n[m[b] - 1], 1u) : 0u;
   if (mask) {
-    uint8_t z[32];
+    uint8_t z[kBinItems];
 #pragma unroll
-    for (int b = 0; b < 32; ++b) z[b] = 0;
-    put_marks(marks, w, V, z);
+    for (int b = 0; b < kBinItems; ++b) z[b] = 0;
+    put_marks(marks, v0, V, z);
+  }
+  const uint32_t inc = wave_incl_scan(tot);
+  if (is_bin && lane() == kWave - 1) s_tmp[t / kWave] = inc;
+  if (blockIdx.x == 0 && is_bin && tot) atomicMin(&s_first, (uint32_t)t);
+  __syncthreads();
+  if (is_bin) {
+    uint32_t before = inc - tot;
+    for (int i = 0; i < t / kWave; ++i) before += s_tmp[i];
+    const uint32_t n = s_n[t];
+    if (n)
+      s_n[t] = before + start +
+               atomicAdd(&set[kSsspBinCursor + copy * kSsspBins + t], n);
+    if (blockIdx.x == 0) {
+      uint32_t* other = bins.state + (bins.set ^ 1) * kSsspBinSet;
+      for (int i = t; i < 2 * kBinCopies * kSsspBins; i += kSsspBins) other[i] = 0u;
+      if (t == kSsspBins - 1) {
+        *out_count = before + tot;
+        const uint32_t f = s_first;
+        other[kSsspBinBase] =
+            set[kSsspBinBase] + (f < (uint32_t)kSsspBins ? f << bins.shift : 0u);
+      }
+    }
   }
   __syncthreads();
-  uint32_t* cur = bins.state + kSsspBinCursor + (blockIdx.x % kBinCopies) * kSsspBins;
-  for (int i = threadIdx.x; i < kSsspBins; i += 256)
-    if (s_n[i]) s_n[i] = atomicAdd(&cur[i], s_n[i]);
-  __syncthreads();
 #pragma unroll
-  for (int b = 0; b < 32; ++b)
-    if ((mask >> b) & 1u) out_q[s_n[m[b] - 1] + rank[b]] = (int32_t)(w * 32 + b);
+  for (int b = 0; b < kBinItems; ++b)
+    if ((mask >> b) & 1u) out_q[s_n[m[b] - 1] + rank[b]] = (int32_t)(v0 + b);
 }
 
 // The same with the near / far split of the priority queue: a marked vertex
@@ -1106,12 +1121,10 @@ hipError_t launch_sssp_mark_compact(uint8_t* marks, int64_t V, const unsigned lo
 hipError_t launch_sssp_bin_compact(uint8_t* marks, int64_t V, const unsigned long long* keys,
                                    DistMirror mirror, uint32_t* relaxed, const SsspBins& bins,
                                    int32_t* out_q, uint32_t* out_count, hipStream_t st) {
-  const int64_t n_words = (V + 31) / 32;
-  if (n_words <= 0) return hipSuccess;
-  const unsigned g = blocks_for(n_words, 256);
+  if (V <= 0) return hipSuccess;
+  const unsigned g = blocks_for(V, 256 * kBinItems);
   k_sssp_bin_count<<<g, 256, 0, st>>>(marks, V, keys, mirror, relaxed, bins);
-  k_sssp_bin_scan<<<1, kSsspBins, 0, st>>>(bins, out_count);
-  k_sssp_bin_scatter<<<g, 256, 0, st>>>(marks, V, bins, out_q);
+  k_sssp_bin_scatter<<<g, 256, 0, st>>>(marks, V, bins, out_q, out_count);
   return hipGetLastError();
 }
 
