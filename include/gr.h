@@ -103,10 +103,11 @@ typedef struct gr_level_trace {
   int32_t kernel;      /* advance kernel: 0 TWC, 1 LB_LIGHT, 2 LB, 3 LB with byte-mark filter,
                           4 pull TWC, 5 pull groups (either over the bitmap, or over the
                           short list of still-unvisited vertices the previous pull level
-                          left), 6 device-predicated step (step_us and
+                          left), 6 step of a device block (step_us and
                           kernel_us are then the block's time divided by its levels),
                           7 SSSP priority-queue refill (far pile split), 8 / 9 / 10 SSSP
-                          TWC / LB_LIGHT / LB relaxation with the byte-mark filter,
+                          TWC / LB_LIGHT / LB relaxation with the byte-mark filter (10:
+                          also its form with the hubs' distance bounds in LDS),
                           11 BFS pull over the list of still-unvisited vertices the
                           previous pull level left (else 4 / 5 pull over the bitmap),
                           12 / 13 / 14 idempotent BFS push TWC / LB_LIGHT / LB
@@ -139,8 +140,9 @@ typedef struct gr_opts {
   gr_level_trace* trace;     /* host array, nullable: per-iteration records */
   int32_t trace_count;       /* out: records written (may exceed capacity; extra are dropped) */
   int32_t device_max_edges;  /* iteration control: while the policy pushes and the frontier has at
-                                most 4096 vertices and at most this many edges, levels run in blocks
-                                of device-predicated steps with one host round trip per block
+                                most 4096 vertices (gr_bfs_multi: 65536 where no row is longer than
+                                64) and at most this many edges, levels run in blocks that the
+                                device steps through by itself, with one host round trip per block
                                 (heuristic and fixed push policies only).  0: default 262144;
                                 < 0: off (one host round trip per level); at most 1 << 24 */
   int32_t sssp_delta;        /* SSSP two-level priority queue (Sec. 5.1, priority queue): improved
@@ -181,7 +183,7 @@ typedef struct gr_opts {
   int32_t bc_dir;            /* gr_bc: how each pass crosses a pair of adjacent levels, a
                                 GR_BC_DIR_* for the forward pass | another << 2 for the backward
                                 pass.  Push: the level the sums come from sweeps its rows and
-                                adds into the other end of each edge with an fp64 atomic; pull:
+                                adds into the other end of each edge (fp64, in LDS first); pull:
                                 the level the sums belong to sweeps its own rows and gathers
                                 them (no atomic per edge).  Auto: per pair, push where the
                                 level the sums come from has under a quarter of the other
@@ -359,8 +361,9 @@ gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* graph, const int32_t* source
  * are processed 16 per pass: every vertex keeps one packed (distance,
  * predecessor) key per source of the pass in one row (4, 8 or 16 slots), the
  * frontier is the union of the sources' frontiers with a per-vertex mask of
- * the sources it is active for, and each (frontier edge, active source) pair
- * is relaxed by one lane, the pairs of an edge on neighbouring lanes.  dist:
+ * the sources it is active for; a lane screens a frontier edge for all sources
+ * with one row of one-byte distance bounds, and the pairs that pass are relaxed
+ * one per lane.  dist:
  * device uint32[k][V] (required), pred: device int32[k][V] or NULL; row s
  * equals gr_sssp with the single source sources[s] (same definitions and
  * canonical predecessors).  Needs weights; GR_ERANGE as gr_sssp.  opts used:
@@ -403,7 +406,7 @@ gr_status gr_bc(gr_ctx* ctx, const gr_graph* graph, const int32_t* sources, int3
  * action, guarded by learned_margin.  Where an iteration is small enough for a
  * block of device-predicated push levels (see device_max_edges) the network
  * may turn the heuristic's pull into a push but not a push into a pull, and
- * the levels inside such a block follow the heuristic.  The choice can only
+ * the levels inside such a block are pushed.  The choice can only
  * change the time taken: every action computes
  * the exact same results.  (The paper picks strategies by fixed thresholds on
  * the degree distribution, Sec. 5.1, and notes in Sec. 7 that the same
