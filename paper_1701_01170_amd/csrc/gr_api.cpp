@@ -727,6 +727,10 @@ constexpr int64_t kSsspMarksDivisor = 16;
 // measured 2.57-2.59 ms with the screen from V / 8, 2.61-2.65 ms from V / 2,
 // 2.76 ms from V and 2.77 ms without it.
 constexpr int64_t kSsspMirrorDivisor = 8;
+// Batched BFS: pushed levels of at least E / this many frontier edges find parents with
+// the pull kernels afterwards, smaller ones with atomic minima in the push.  R-MAT 20,
+// 64 sources, a level of 1.1 M of 31 M edges: 52 us against 29 + 40; of 25 M: 5.9 ms against 1.9.
+constexpr int64_t kMsSearchDivisor = 8;
 // Degree-ordered graphs: iterations with at least kHotMinEdges frontier edges, rows of
 // kHotMinDegree edges on average, relax with the hubs' mirror in LDS
 // (k_sssp_relax_hot).  Below, the table's load (32 MB through the L2s) and the search
@@ -1839,9 +1843,13 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
           GR_HIP(launch_frontier_offsets(q[cur], n_a, g->R, bsums, offsets, rstart,
                                          chunks, adv.chunk, st));
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k0, st));
+        const bool search = parent && m_a >= E / kMsSearchDivisor;
         GR_HIP(launch_ms_push(mode, q[cur], offsets, rstart, chunks, n_a, m_a, g->R, g->C,
-                              front[fc], visit, next, out, V, g->perm, q[(cur + 1) % 3],
+                              front[fc], visit, next, out, V, g->perm, !search, q[(cur + 1) % 3],
                               &ctrl->q_count[(cur + 1) % 3], adv, st));
+        if (search)
+          GR_HIP(launch_ms_pull(V, E, g->max_degree, g->R, g->C, front[fc], visit, full, next,
+                                nullptr, nullptr, out, g->perm, offsets, rstart, ctrl->ms_big, st));
         if (tracing) GR_HIP(hipEventRecord(ctx->ev_k1, st));
       }
       rs.action_count[action]++;

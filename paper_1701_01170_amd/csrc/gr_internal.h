@@ -468,10 +468,11 @@ hipError_t launch_ms_push(int mode, const int32_t* active, const int32_t* offset
                           int64_t m_a, const int32_t* R, const int32_t* C,
                           const unsigned long long* front, const unsigned long long* visit,
                           unsigned long long* next, const MsOut& o, int64_t V, const int32_t* perm,
-                          int32_t* touched, uint32_t* n_touched, const AdvCfg& cfg, hipStream_t st);
+                          bool parents, int32_t* touched, uint32_t* n_touched, const AdvCfg& cfg, hipStream_t st);
 // The pull writes the parents of the pairs it reaches.  mid_q, hub_q: [V] lists
 // of the longer rows, n_big[2] their counters (zero before; launch_ms_finalize
-// zeroes them again).
+// zeroes them again).  touched null: after a push without parents, writes those of
+// the pairs in next.
 hipError_t launch_ms_pull(int64_t V, int64_t E, int64_t max_degree, const int32_t* R,
                           const int32_t* C, const unsigned long long* front,
                           const unsigned long long* visit, unsigned long long full,

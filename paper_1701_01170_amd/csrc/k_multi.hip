@@ -48,7 +48,9 @@ struct MsParents {
 // parents (no returning atomic; a pair's word starts at 0xffffffff).  A search by
 // the finalize pass instead scanned every touched vertex's row up to the last of
 // its new parents: 109 K hubs reached by 204 K edges took 1.58 ms of an R-MAT 20
-// batch.
+// batch.  Where a level pushes much of the graph the atomics are the larger cost (25 M
+// and 31 M edges: 5.9 and 8.2 ms with them, 1.1 and 0.8 without); there the pull
+// kernels find the parents afterwards (0.9 and 0.4 ms; kMsSearchDivisor).
 template <bool PARENT>
 struct MsPush {
   const u64* __restrict__ visit;
@@ -143,7 +145,8 @@ __device__ __forceinline__ int32_t ms_first(const int32_t (&u)[kMsU], const u64 
 // their end, so the split has to balance edges: with every long row left to the
 // wavefront that owns the vertex, the first 64 vertices of a degree-ordered
 // graph shared one wavefront (R-MAT 20, 64 sources: 10.2 ms of a level's
-// 10.3 ms).  This kernel scans the rows of up to kMsLaneMax neighbours, one lane
+// 10.3 ms).  With touched null the level was pushed without parents: the rows are
+// scanned for the bits in next, only their parents are written.  This kernel scans the rows of up to kMsLaneMax neighbours, one lane
 // each, and lists the longer ones for the two kernels below.
 __global__ __launch_bounds__(256) void k_ms_pull(int64_t V, const int32_t* __restrict__ R,
                                                  const int32_t* __restrict__ C,
@@ -161,7 +164,7 @@ __global__ __launch_bounds__(256) void k_ms_pull(int64_t V, const int32_t* __res
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const int64_t v = v0 + k * 256;
-    need[k] = v < V ? full & ~visit[v] : 0ull;
+    need[k] = v < V ? (touched ? full & ~visit[v] : next[v]) : 0ull;
   }
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -200,15 +203,18 @@ __global__ __launch_bounds__(256) void k_ms_pull(int64_t V, const int32_t* __res
         }
       }
     }
-    if (acc) {
+    if (acc && touched) {
       next[v] = acc;
       hits |= 1u << k;
     }
   }
-  uint32_t slot = block_append<256>(__popc(hits), n_touched);
+  uint32_t slot;
+  if (touched) {
+    slot = block_append<256>(__popc(hits), n_touched);
 #pragma unroll
-  for (int k = 0; k < K; ++k)
-    if ((hits >> k) & 1u) touched[slot++] = (int32_t)(v0 + k * 256);
+    for (int k = 0; k < K; ++k)
+      if ((hits >> k) & 1u) touched[slot++] = (int32_t)(v0 + k * 256);
+  }
   if (mid_q) {
     slot = block_append<256>(__popc(mids), &n_big[0]);
 #pragma unroll
@@ -242,7 +248,7 @@ __global__ __launch_bounds__(256) void k_ms_pull_mid(
     u64 lneed = 0;
     if (lane() < cnt) {
       lv = list[i0 + lane()];
-      lneed = full & ~visit[lv];
+      lneed = touched ? full & ~visit[lv] : next[lv];
       lrb = R[lv];
       lre = R[lv + 1];
     }
@@ -272,11 +278,11 @@ __global__ __launch_bounds__(256) void k_ms_pull_mid(
       }
       if (fnd) {
         if (par.p && pu >= 0) par.p[(int64_t)lane() * par.ps + par.at(v)] = par.id(pu);
-        if (lane() == 0) next[v] = fnd;
+        if (lane() == 0 && touched) next[v] = fnd;
         hits |= 1u << k;
       }
     }
-    if (hits) {
+    if (hits && touched) {
       uint32_t base = 0;
       if (lane() == 0) base = atomicAdd(n_touched, (uint32_t)__popc(hits));
       base = __shfl(base, 0);
@@ -302,7 +308,7 @@ __global__ __launch_bounds__(kMsHubBlock) void k_ms_pull_hub(
   int buf = 0;
   for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
     const int32_t v = list[i];
-    const u64 nd = full & ~visit[v];
+    const u64 nd = touched ? full & ~visit[v] : next[v];
     const uint32_t rb = (uint32_t)R[v], re = (uint32_t)R[v + 1];
     const int64_t pv = par.p ? par.at(v) : 0;
     u64 fnd = 0;
@@ -332,7 +338,7 @@ __global__ __launch_bounds__(kMsHubBlock) void k_ms_pull_hub(
       fnd |= all;
       buf ^= 1;
     }
-    if (threadIdx.x == 0 && fnd) {
+    if (threadIdx.x == 0 && fnd && touched) {
       next[v] = fnd;
       touched[atomicAdd(n_touched, 1u)] = v;
     }
@@ -563,10 +569,10 @@ hipError_t launch_ms_push(int mode, const int32_t* active, const int32_t* offset
                           const int32_t* rstart, const int32_t* chunk_start, int64_t n_a,
                           int64_t m_a, const int32_t* R, const int32_t* C, const u64* front,
                           const u64* visit, u64* next, const MsOut& o, int64_t V,
-                          const int32_t* perm, int32_t* touched, uint32_t* n_touched,
-                          const AdvCfg& cfg, hipStream_t st) {
+                          const int32_t* perm, bool parents, int32_t* touched,
+                          uint32_t* n_touched, const AdvCfg& cfg, hipStream_t st) {
   const MsParents par = parents_of(o, V, perm);
-  if (par.p)
+  if (par.p && parents)
     return push_dispatch(mode, active, offsets, rstart, chunk_start, n_a, m_a, R, C,
                          MsPush<true>{visit, next, front, par}, touched, n_touched, cfg, st);
   return push_dispatch(mode, active, offsets, rstart, chunk_start, n_a, m_a, R, C,

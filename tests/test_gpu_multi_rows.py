@@ -4,6 +4,8 @@ import numpy as np
 import pytest
 
 import oracle
+import paper_1701_01170_amd as gr
+from paper_1701_01170_amd import graphgen as gg
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +56,22 @@ def test_tiers_planes_and_widths(ctx, k, renumber):
             np.testing.assert_array_equal(p[i].cpu().numpy(), np.where(ed <= cap, ep, -1), err_msg=f"{kw} {s}")
             np.testing.assert_array_equal(d0[i].cpu().numpy(), np.where(ed <= cap, ed, -1), err_msg=f"{kw} {s}")
     g.free()
+
+
+@pytest.mark.parametrize("k", [1, 5, 64])
+@pytest.mark.parametrize("action", [gr.PUSH_LB, gr.PUSH_TWC])
+def test_parents_of_large_pushed_levels(ctx, k, action):
+    """Every level pushed: small ones take parents by atomic minima, large ones search them over rows of each length."""
+    rng = np.random.default_rng(k)
+    hub = [(0, v) for v in range(1, 5000)] + [(1, v) for v in range(2, 1500)] + [(2, v) for v in range(3, 60)]
+    e = np.concatenate([np.array(hub), rng.integers(0, 6000, (40000, 2))])
+    for h in (gg.rmat(13, 16, seed=31), gg.sort_adjacency(gg.from_edges(6000, e[e[:, 0] != e[:, 1]], symmetric=True))):
+        srcs = [int(s) for s in gg.sources(h, k, seed=17)]
+        ed, ep = oracle.bfs_multi(h.row_offsets, h.col_indices, srcs)
+        for renumber in (False, True):
+            g = gr.Graph.from_host(ctx, h, symmetric=True, renumber=renumber)
+            o = gr.default_opts(policy=gr.POLICY_FIXED, fixed_action=action, device_max_edges=-1)
+            d, p, _ = gr.bfs_multi(g, srcs, opts=o)
+            np.testing.assert_array_equal(d.cpu().numpy(), ed)
+            np.testing.assert_array_equal(p.cpu().numpy(), ep)
+            g.free()
