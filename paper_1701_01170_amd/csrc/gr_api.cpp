@@ -739,6 +739,9 @@ constexpr int64_t kMsSearchDivisor = 8;
 // 0.06 -> 0.12 ms.
 constexpr int64_t kHotMinEdges = 1 << 22;
 constexpr int64_t kHotMinDegree = 64;
+// ... and at least this many chunks per CU (one per wavefront): R-MAT 20 at 16384 edges
+// per chunk 2.7 ms without this bound, 2.0 with it.
+constexpr int64_t kHotMinChunks = 16;
 
 constexpr int64_t kTeamHalfMaxV = 3 << 20;
 struct DlPlan {
@@ -1363,7 +1366,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
     GR_TRY(pool_typed(ctx, S_FAR_TAGS, V, &pq.far_tag));
   }
   // distance bins of the marks compaction
-  SsspBins bins{nullptr, 0u, 0};
+  SsspBins bins{nullptr, 0u, 0, false};
   if (!use_pq && !(opts.sssp_opt_off & GR_SSSP_OPT_BINS)) {
     GR_TRY(pool_typed(ctx, S_SSSP_BINS, kSsspBinWords, &bins.state));
     bins.shift = bin_shift_for(g->max_weight);
@@ -1564,7 +1567,8 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
         kernel += kTraceMarksOffset;
         const bool screen = expanded + n_f + far_n >= V / kSsspMirrorDivisor;
         const int64_t n_hot = perm && mode == 2 && m_f >= kHotMinEdges &&
-                                      m_f >= kHotMinDegree * n_f
+                                      m_f >= kHotMinDegree * n_f &&
+                                      m_f >= kHotMinChunks * ctx->cu_count * adv.chunk
                                   ? std::min<int64_t>(V, kHotVertices) : 0;
         GR_HIP(launch_sssp_relax_marks(mode, q[cur], offsets, rstart, chunks, n_f, m_f, g->R, g->C,
                                        g->W, keys, perm, marks, mirror, relaxed, screen, n_hot,
@@ -1574,6 +1578,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
           GR_HIP(launch_sssp_pq_mark_compact(marks, V, keys, mirror, relaxed, pq, ctrl,
                                              q[(cur + 1) % 3], &ctrl->q_count[(cur + 1) % 3], st));
         else if (bins.state) {
+          bins.spread = mode == 0;
           GR_HIP(launch_sssp_bin_compact(marks, V, keys, mirror, relaxed, bins, q[(cur + 1) % 3],
                                          &ctrl->q_count[(cur + 1) % 3], st));
           bins.set ^= 1;

@@ -684,6 +684,7 @@ struct SsspBins {
   uint32_t* state;  // kSsspBinWords words
   uint32_t shift;   // bin width 2^shift
   int set;          // 0 or 1: the set of this call; the next call takes the other
+  bool spread;      // neighbouring vertices apart in the list (the TWC advance reads it)
 };
 hipError_t launch_sssp_bin_compact(uint8_t* marks, int64_t V, const unsigned long long* keys,
                                    DistMirror mirror, uint32_t* relaxed, const SsspBins& bins,

@@ -24,7 +24,8 @@ def test_equals_oracle(ctx, n, lo, hi):
         g = gr.Graph.from_host(ctx, h, symmetric=True, renumber=renumber)
         for s in (srcs[:1], srcs):
             ed, ep = oracle.sssp(h.row_offsets, h.col_indices, h.weights, s)
-            for kw in ({}, dict(device_max_edges=-1), dict(device_max_edges=-1, sssp_opt_off=gr.SSSP_OPT_CULL)):
+            for kw in ({}, dict(device_max_edges=-1), dict(device_max_edges=-1, sssp_opt_off=gr.SSSP_OPT_CULL),
+                       dict(device_max_edges=-1, policy=gr.POLICY_FIXED, fixed_action=gr.PUSH_TWC)):
                 d, p, _ = gr.sssp(g, s, opts=gr.default_opts(**kw))
                 np.testing.assert_array_equal(d.cpu().numpy().view(np.uint32), ed, err_msg=str(kw))
                 np.testing.assert_array_equal(p.cpu().numpy(), ep, err_msg=str(kw))
