@@ -37,6 +37,11 @@
  *     (60 s, or GR_WAIT_LIMIT_MS from the environment when the context is
  *     created); past it they return GR_EHIP, and the context must then be
  *     destroyed, since its stream may still hold the unfinished work.
+ *   - Small levels of gr_bfs / gr_sssp run on a team of workgroups that wait
+ *     for one another; on a chip full of other work they give up after a
+ *     bounded number of polls and the levels run without a team.
+ *     GR_TEAM_POLLS from the environment, read when the context is created,
+ *     sets that number (0: never a team).  Results are the same.
  */
 #ifndef GR_H
 #define GR_H

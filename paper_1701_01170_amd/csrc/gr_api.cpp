@@ -310,6 +310,9 @@ extern "C" gr_status gr_ctx_create(int32_t device, gr_ctx** out) {
     const long long ms = std::atoll(w);
     if (ms > 0) c->wait_limit = std::chrono::milliseconds(ms);
   }
+  c->team_polls = kTeamJoinPolls;
+  if (const char* w = std::getenv("GR_TEAM_POLLS"); w && *w)
+    c->team_polls = (int32_t)std::min(std::max(std::atoll(w), 0ll), 1ll << 24);
   // control block mirror, block log and publish flag: coherent, device-mapped
   // pinned memory
   void* hc = nullptr;
@@ -1064,6 +1067,7 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
         da.max_steps = max_steps;
         da.team = bsums;  // (the statistics are through with them)
         da.log_w = dl.log_w;
+        da.team_polls = ctx->team_polls;
         const bool team = !(i & 1);
         GR_HIP(launch_bfs_dstep(da, bm, p, depth, parent, perm, level + 1, team,
                                 team ? dl.team_blocks : dl.blocks, es));
@@ -1476,6 +1480,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
         da.max_steps = max_steps;
         da.team = bsums;  // (the statistics and the degree scan are through with them)
         da.log_w = dl.log_w;
+        da.team_polls = ctx->team_polls;
         const bool team = !(i & 1);
         const int blocks = team ? dl.team_blocks : dl.blocks;
         if (use_pq)

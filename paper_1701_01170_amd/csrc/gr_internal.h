@@ -156,6 +156,9 @@ struct gr_ctx {
   // Longest wait for one published control block before a traversal gives up
   // with GR_EHIP (environment GR_WAIT_LIMIT_MS at context creation, default 60 s).
   std::chrono::milliseconds wait_limit{60000};
+  // Polls before a member of a team of workgroups calls the team off (environment
+  // GR_TEAM_POLLS at context creation; 0: at once, so that no team runs).
+  int32_t team_polls = 0;
   hipEvent_t ev_start = nullptr, ev_stop = nullptr, ev_a = nullptr, ev_b = nullptr;
   hipEvent_t ev_k0 = nullptr, ev_k1 = nullptr;  // around the advance kernel when tracing
   hipEvent_t ev_c0 = nullptr, ev_c1 = nullptr;  // around a whole call that runs BFS inside
@@ -556,6 +559,7 @@ hipError_t launch_publish_select(const MlpSelect& m, Ctrl* ctrl, Ctrl* host_dst,
 constexpr int kDlMaxN = 4096;        // frontier vertices staged in LDS per level
 constexpr int kTeamMaxM = 1 << 15;   // edges of a k_team level
 constexpr int kTeamMaxStaged = 2048; // vertices of one where every workgroup stages them all
+constexpr int kTeamJoinPolls = 1 << 14;  // polls before a member calls its team off
 constexpr int kTeamWords = 40;       // k_team kernels of one block
 constexpr int kBlockMaxSteps = 4096; // levels of one block (bounds the time of one kernel)
 constexpr int kDpMaxN = 1 << 16;     // frontier vertices of a k_dpush level (graphs without long rows)
@@ -578,14 +582,15 @@ struct DlArgs {
   int32_t edges_vs_all = 0;   // 1: push -> pull when m_f > E * do_a (batched BFS's rule)
   // k_dstep and k_team: the queues, the block's first one, this kernel's place in
   // the block and the block's most levels (q_cur, q_next, cur, step: k_dpush);
-  // k_team: its words [kTeamWords] and the log2 of the edge slots per vertex where no
-  // row is longer (-1: rows of any length)
+  // k_team: its words [kTeamWords], the log2 of the edge slots per vertex where no
+  // row is longer (-1: rows of any length), and the polls of its start
   Queues3 qs = {};
   int32_t cur0 = 0;
   int32_t seq = 0;
   int32_t max_steps = 1 << 30;
   int64_t* team = nullptr;
   int32_t log_w = -1;
+  int32_t team_polls = kTeamJoinPolls;
 };
 // mf: edges of the first frontier (k_dpush levels only); team: the k_team words,
 // cleared (nullable)

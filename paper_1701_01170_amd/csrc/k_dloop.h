@@ -30,6 +30,7 @@
 #pragma once
 
 #include "k_advance.h"
+#include "team_join.h"
 
 namespace gr {
 
@@ -189,10 +190,10 @@ __global__ __launch_bounds__(kAdvBlock) void k_dstep(DlArgs a, F f) {
 // to be written back to memory in between, which the caches of different XCDs would
 // need (and which made a barrier over the whole chip slower than a kernel boundary).
 // Whoever runs elsewhere leaves at once.  Members register in one word together with
-// the total of workgroups seen; when all have been seen, all members run at the same
-// time and know their number.  If that takes too long (the chip is full of other
-// work) the first to give up calls the run off for all of them, and the block's other
-// kernels do the levels.  One workgroup alone has the same latency per trip, but its CU's
+// the total of workgroups seen (team_join.h); when all have been seen, all members run
+// at the same time and know their number.  If that takes too long (the chip is full of
+// other work) the first to give up calls the run off for all of them, and the block's
+// other kernels do the levels.  One workgroup alone has the same latency per trip, but its CU's
 // throughput bounds levels of more than some 2 K edges (6.7 K edges: 32 us).
 //
 // Rows of at most 8 (a.log_w >= 0): a workgroup takes an equal slice of the
@@ -201,10 +202,10 @@ __global__ __launch_bounds__(kAdvBlock) void k_dstep(DlArgs a, F f) {
 // k_dstep.  Either way the arrival word of the level's barrier also adds up the new
 // frontier's vertices and (sliced) edges.
 struct TeamWord {       // one per kernel of a block, zero at its start
-  uint32_t reg;         // workgroups seen | members << 16
-  uint32_t state;       // 0 undecided, 1 go, 2 off
-  uint32_t q_count[3];  // append counters, rotating by level
+  uint32_t reg;         // registration word (team_join.h)
   uint32_t pad;
+  uint32_t q_count[3];  // append counters, rotating by level
+  uint32_t pad1;
   unsigned long long arrive[3];  // arrivals | vertices << 8 | edges << 32, rotating by level
   uint32_t pad2[4];
 };
@@ -217,34 +218,31 @@ __device__ __forceinline__ uint32_t xcc_id() {
   return __builtin_amdgcn_s_getreg((4 - 1) << 11 | 0 << 6 | 20) & 0xfu;
 }
 
-constexpr int kTeamJoinPolls = 1 << 14;   // polls before a member gives the start up
 constexpr int kTeamWaitPolls = 1 << 22;   // polls of a level's barrier: far beyond any level
+
+struct TeamRegWord {  // the registration word in memory (team_join.h)
+  uint32_t* p;
+  __device__ __forceinline__ uint32_t add(uint32_t x) { return atomicAdd(p, x); }
+  __device__ __forceinline__ uint32_t load() {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ uint32_t cas(uint32_t e, uint32_t x) { return atomicCAS(p, e, x); }
+};
 
 // Joins the team of kernel word t: the member's index and the team's size, or -1 to
 // leave.  Called by every thread.
-__device__ __forceinline__ int team_join(TeamWord* t, int* size) {
+__device__ __forceinline__ int team_join(TeamWord* t, int polls, int* size) {
   __shared__ int s_idx, s_size;
   if (threadIdx.x == 0) {
-    const bool member = xcc_id() == 0;
-    const uint32_t old = atomicAdd(&t->reg, member ? 0x10001u : 1u);
-    int idx = member ? (int)(old >> 16) : -1;
-    uint32_t now = old + (member ? 0x10001u : 1u);
-    if (member) {
-      uint32_t want = 1;
+    TeamRegWord w{&t->reg};
+    TeamJoin j(gridDim.x, xcc_id() == 0, polls);
 #pragma unroll 1
-      for (int i = 0; (now & 0xffffu) != gridDim.x; ++i) {
-        if (i >= kTeamJoinPolls) {
-          want = 2;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-        now = __hip_atomic_load(&t->reg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      const uint32_t was = atomicCAS(&t->state, 0u, want);
-      if ((was ? was : want) != 1u) idx = -1;
+    while (j.next != TeamJoin::kDone) {
+      if (j.next == TeamJoin::kPoll) __builtin_amdgcn_s_sleep(1);
+      j.step(w);
     }
-    s_idx = idx;
-    s_size = (int)(now >> 16);
+    s_idx = j.index;
+    s_size = j.size;
   }
   __syncthreads();
   *size = s_size;
@@ -300,7 +298,7 @@ __global__ __launch_bounds__(kAdvBlock) void k_team(DlArgs a, F f) {
   const bool sliced = a.log_w >= 0;
   if (!sliced && n0 > (uint32_t)kTeamMaxStaged) return;  // nothing to run here
   int size;
-  const int me = team_join(tw, &size);
+  const int me = team_join(tw, a.team_polls, &size);
   if (me < 0) return;
   const int w = threadIdx.x / kWave;
   int step = step0;
