@@ -257,7 +257,10 @@ __device__ __forceinline__ int team_join(TeamWord* t, int polls, int* size) {
 __device__ __forceinline__ unsigned long long team_barrier(unsigned long long* w, int size,
                                                            uint32_t n, uint32_t m) {
   __shared__ unsigned long long s_x;
-  __builtin_amdgcn_s_waitcnt(0);  // this wavefront's stores and atomics are acknowledged
+  // this wavefront's stores and atomics are acknowledged.  (As the builtin, the wait
+  // would not be declared to touch memory: the compiler could place a store after it, and
+  // the workgroup fence of __syncthreads does not wait for one.)
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned long long add = 1ull | (unsigned long long)n << 8 | (unsigned long long)m << 32;
@@ -315,8 +318,10 @@ __global__ __launch_bounds__(kAdvBlock) void k_team(DlArgs a, F f) {
   // one's may still be polled
   auto rotate = [&]() {
     if (me == 0 && threadIdx.x == 0) {
-      tw->arrive[(it + 1) % 3] = 0ull;
-      tw->q_count[(it + 1) % 3] = 0u;
+      __hip_atomic_store(&tw->arrive[(it + 1) % 3], 0ull, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&tw->q_count[(it + 1) % 3], 0u, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
     }
   };
   while (step < a.max_steps) {
