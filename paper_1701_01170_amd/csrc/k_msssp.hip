@@ -42,6 +42,7 @@
 // below T join the frontier, pairs still above stay, pairs whose distance fell
 // below the old threshold meanwhile were expanded with it already and are
 // dropped.  Results are unchanged.
+#include "edge_range.h"
 #include "k_advance.h"
 
 namespace gr {
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(256) void k_msssp_relax(
     __syncthreads();
     const int32_t lo = (int32_t)(e0 > s_off[0] ? e0 : s_off[0]);
     const int32_t hi = (int32_t)(e1 < s_off[cnt] ? e1 : s_off[cnt]);
-    for (int64_t b0 = lo + wv * kWave; b0 < hi; b0 += BLOCK * B) {
+    for (int64_t b0 = wave_first_edge(lo, wv); b0 < hi; b0 += BLOCK * B) {
       int32_t v[B], k[B];
       uint32_t w[B];
       Row row[B];
