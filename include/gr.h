@@ -235,7 +235,9 @@ typedef struct gr_run_stats {
   int64_t teps_edges;        /* sum of degrees of reached vertices, summed over sources (Sec. 7 TEPS) */
   int64_t inspected_edges;   /* edges read by advance (push: m_f; pull: neighbours scanned) */
   float device_ms;           /* event-timed device time of the call (after validation/setup) */
-  int32_t pad;
+  int32_t team_levels;       /* gr_bfs, gr_sssp: iterations that ran on a team of workgroups inside
+                                a device block; negative: minus the number of teams that could not
+                                form (the chip was full), after which the call used none; else 0 */
 } gr_run_stats;
 
 typedef struct gr_graph_info {

@@ -75,12 +75,12 @@ class Opts(ctypes.Structure):
 class RunStats(ctypes.Structure):
     _fields_ = [("iterations", ctypes.c_int32), ("action_count", ctypes.c_int32 * 4),
                 ("teps_edges", ctypes.c_int64), ("inspected_edges", ctypes.c_int64),
-                ("device_ms", ctypes.c_float), ("pad", ctypes.c_int32)]
+                ("device_ms", ctypes.c_float), ("team_levels", ctypes.c_int32)]
 
     def as_dict(self) -> dict:
         return dict(iterations=self.iterations, action_count=list(self.action_count),
                     teps_edges=self.teps_edges, inspected_edges=self.inspected_edges,
-                    device_ms=self.device_ms)
+                    device_ms=self.device_ms, team_levels=self.team_levels)
 
 
 class GraphInfo(ctypes.Structure):

@@ -754,9 +754,20 @@ struct DlPlan {
   int blocks = 256;
   int team_blocks = 256;  // of the kernels that run several levels
   int64_t* log = nullptr;
+  bool team = true;     // until a team was called off: the rest of the call runs without
+  int64_t team_levels = 0, teams_off = 0;
   bool graph = false;   // record each block as a hipGraph
   int log_w = -1;       // DlArgs::log_w of the graph
+  int graph_key(int kind) const { return (kind << 8) | (team ? 0 : 1 << 7) | len; }
+  // a block's read-back
+  void take_teams(const Ctrl* hc) {
+    team_levels += hc->dl_team;
+    teams_off += hc->dl_team_off;
+    if (hc->dl_team_off) team = false;
+  }
+  int32_t stat() const { return (int32_t)(teams_off ? -teams_off : team_levels); }
 };
+static_assert(kDlMaxPairs < 1 << 7, "a block's length in its graph key");
 constexpr int kGraphKeyBfs = 0, kGraphKeySssp = 1, kGraphKeySsspPq = 2;
 
 // The most levels of a block that starts at level `level` (tracing: what its log
@@ -1068,11 +1079,11 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
         da.team = bsums;  // (the statistics are through with them)
         da.log_w = dl.log_w;
         da.team_polls = ctx->team_polls;
-        const bool team = !(i & 1);
+        const bool team = dl.team && !(i & 1);
         GR_HIP(launch_bfs_dstep(da, bm, p, depth, parent, perm, level + 1, team,
                                 team ? dl.team_blocks : dl.blocks, es));
       }
-      if (dl.graph) GR_TRY(block_capture_launch(ctx, &capture, (kGraphKeyBfs << 8) | dl.len, st));
+      if (dl.graph) GR_TRY(block_capture_launch(ctx, &capture, dl.graph_key(kGraphKeyBfs), st));
       if (tracing) GR_HIP(hipEventRecord(ctx->ev_b, st));
       // statistics of the frontier the block leaves (found on the device),
       // then a single read-back; with k == 0 levels run the frontier is
@@ -1089,6 +1100,7 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
                        tracing ? &lgx : nullptr));
       const int k = hc->dl_levels;
       if (hc->dl_fail) return fail(GR_EHIP, "a device-side wait of a block of levels ran out");
+      dl.take_teams(hc);
       if (k > 0) {
         const int64_t* lg = ctx->host_dlog;  // the block's level log (host copy)
         float block_ms = 0.f;
@@ -1247,6 +1259,7 @@ gr_status bfs_run(gr_ctx* ctx, const gr_graph* g, int32_t source, int32_t* depth
     rs.iterations = level;
     // when stopped early the last frontier is reached but not expanded
     rs.teps_edges = visited_m;
+    rs.team_levels = dl.stat();
     rs.inspected_edges = inspected_push + hc->inspected;
     rs.device_ms = ms;
     *stats = rs;
@@ -1481,7 +1494,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
         da.team = bsums;  // (the statistics and the degree scan are through with them)
         da.log_w = dl.log_w;
         da.team_polls = ctx->team_polls;
-        const bool team = !(i & 1);
+        const bool team = dl.team && !(i & 1);
         const int blocks = team ? dl.team_blocks : dl.blocks;
         if (use_pq)
           GR_HIP(launch_sssp_pq_dstep(da, g->W, keys, tags, it + 1, pq, team, blocks, es));
@@ -1490,7 +1503,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
       }
       if (dl.graph)
         GR_TRY(block_capture_launch(ctx, &capture,
-                                    ((use_pq ? kGraphKeySsspPq : kGraphKeySssp) << 8) | dl.len, st));
+                                    dl.graph_key(use_pq ? kGraphKeySsspPq : kGraphKeySssp), st));
       if (tracing) GR_HIP(hipEventRecord(ctx->ev_b, st));
       // statistics of the frontier the block leaves, then a single read-back
       // (with k == 0 levels run the statistics just move to the other slot)
@@ -1505,6 +1518,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
                        tracing ? &lgx : nullptr));
       const int k = hc->dl_levels;
       if (hc->dl_fail) return fail(GR_EHIP, "a device-side wait of a block of levels ran out");
+      dl.take_teams(hc);
       if (use_pq) {
         pq.T = hc->pq_T[k & 1];
         pq.epoch = hc->pq_epoch[k & 1];
@@ -1625,6 +1639,7 @@ extern "C" gr_status gr_sssp(gr_ctx* ctx, const gr_graph* g, const int32_t* sour
     GR_TRY(elapsed_ms(ctx->ev_start, ctx->ev_stop, &ms));
     rs.iterations = it;
     rs.teps_edges = hc->reached_edges;
+    rs.team_levels = dl.stat();
     rs.inspected_edges = inspected;
     rs.device_ms = ms;
     *stats = rs;

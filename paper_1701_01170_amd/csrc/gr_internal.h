@@ -108,7 +108,8 @@ struct Ctrl {
   uint32_t ul_count[2];     // BFS pull: lengths of the two unvisited lists
   uint32_t ms_big[2];       // batched BFS pull: rows listed for the wavefront / workgroup tier
   int32_t dl_step[2];       // levels of the block that ran, as the block's next kernel reads it
-  uint32_t pad3[2];
+  int32_t dl_team;          // levels of the block that teams ran
+  uint32_t dl_team_off;     // teams of the block that were called off (later ones are not tried)
   // device-predicated level blocks (iteration control without host round trips)
   int32_t dl_levels;        // levels of the current block that ran
   int32_t dl_stop;          // a level of the block declined to run
@@ -157,7 +158,7 @@ struct gr_ctx {
   // with GR_EHIP (environment GR_WAIT_LIMIT_MS at context creation, default 60 s).
   std::chrono::milliseconds wait_limit{60000};
   // Polls before a member of a team of workgroups calls the team off (environment
-  // GR_TEAM_POLLS at context creation; 0: at once, so that no team runs).
+  // GR_TEAM_POLLS at context creation; 0: no team forms).
   int32_t team_polls = 0;
   hipEvent_t ev_start = nullptr, ev_stop = nullptr, ev_a = nullptr, ev_b = nullptr;
   hipEvent_t ev_k0 = nullptr, ev_k1 = nullptr;  // around the advance kernel when tracing

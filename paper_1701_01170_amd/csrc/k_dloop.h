@@ -192,8 +192,8 @@ __global__ __launch_bounds__(kAdvBlock) void k_dstep(DlArgs a, F f) {
 // Whoever runs elsewhere leaves at once.  Members register in one word together with
 // the total of workgroups seen (team_join.h); when all have been seen, all members run
 // at the same time and know their number.  If that takes too long (the chip is full of
-// other work) the first to give up calls the run off for all of them, and the block's
-// other kernels do the levels.  One workgroup alone has the same latency per trip, but its CU's
+// other work) the first to give up calls the run off for all of them, the block's other
+// kernels do the levels, and the rest of the call runs without teams.  One workgroup alone has the same latency per trip, but its CU's
 // throughput bounds levels of more than some 2 K edges (6.7 K edges: 32 us).
 //
 // Rows of at most 8 (a.log_w >= 0): a workgroup takes an equal slice of the
@@ -230,17 +230,20 @@ struct TeamRegWord {  // the registration word in memory (team_join.h)
 };
 
 // Joins the team of kernel word t: the member's index and the team's size, or -1 to
-// leave.  Called by every thread.
-__device__ __forceinline__ int team_join(TeamWord* t, int polls, int* size) {
+// leave; whoever calls the team off counts it in the control block.  Called by every
+// thread.
+__device__ __forceinline__ int team_join(TeamWord* t, int polls, Ctrl* ctrl, int* size) {
   __shared__ int s_idx, s_size;
   if (threadIdx.x == 0) {
     TeamRegWord w{&t->reg};
-    TeamJoin j(gridDim.x, xcc_id() == 0, polls);
+    // (polls 0: a count that is never complete, so that no team forms)
+    TeamJoin j(gridDim.x + (polls == 0 ? 1u : 0u), xcc_id() == 0, polls);
 #pragma unroll 1
     while (j.next != TeamJoin::kDone) {
       if (j.next == TeamJoin::kPoll) __builtin_amdgcn_s_sleep(1);
       j.step(w);
     }
+    if (j.called_off) atomicAdd(&ctrl->dl_team_off, 1u);
     s_idx = j.index;
     s_size = j.size;
   }
@@ -298,10 +301,14 @@ __global__ __launch_bounds__(kAdvBlock) void k_team(DlArgs a, F f) {
   const uint32_t n0 = ctrl->q_count[(a.cur0 + step0) % 3];
   // the levels so far, in case nobody runs any here (they only grow)
   if (blockIdx.x == 0 && threadIdx.x == 0) atomicMax(&ctrl->dl_step[(a.seq + 1) & 1], step0);
+  // a team that could not form waited in vain: the block's later ones are not tried (a
+  // workgroup that reads this late, in the kernel whose team was called off, would find
+  // that in the word)
+  if (ctrl->dl_team_off) return;
   const bool sliced = a.log_w >= 0;
   if (!sliced && n0 > (uint32_t)kTeamMaxStaged) return;  // nothing to run here
   int size;
-  const int me = team_join(tw, a.team_polls, &size);
+  const int me = team_join(tw, a.team_polls, ctrl, &size);
   if (me < 0) return;
   const int w = threadIdx.x / kWave;
   int step = step0;
@@ -522,6 +529,7 @@ __global__ __launch_bounds__(kAdvBlock) void k_team(DlArgs a, F f) {
     atomicMax(&ctrl->dl_step[(a.seq + 1) & 1], step);
     if (step != step0) {
       ctrl->dl_levels = step;
+      ctrl->dl_team += step - step0;
       ctrl->q_count[cur] = (uint32_t)n;
       ctrl->q_count[(cur + 1) % 3] = 0;
       ctrl->q_count[(cur + 2) % 3] = 0;

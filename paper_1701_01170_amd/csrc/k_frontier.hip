@@ -311,6 +311,8 @@ __global__ __launch_bounds__(kStatsGrid) void k_dl_begin(Ctrl* __restrict__ ctrl
   ctrl->dl_mf[0] = mf;
   ctrl->dl_step[0] = ctrl->dl_step[1] = 0;
   ctrl->dl_fail = 0;
+  ctrl->dl_team = 0;
+  ctrl->dl_team_off = 0;
   ctrl->pq_T[0] = pq_T;
   ctrl->pq_epoch[0] = pq_epoch;
   ctrl->pq_fc[0] = pq_fc;

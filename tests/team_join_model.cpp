@@ -29,7 +29,7 @@ struct State {
   }
 };
 
-int members;
+int members, expected;
 std::set<std::vector<long>> seen;
 
 void bad(const State& s, const char* what) {
@@ -53,6 +53,7 @@ void check_end(const State& s) {
   }
   if ((int)places.size() != in) bad(s, "two members with one place");
   if (in != 0 && in != members) bad(s, "only some members run");
+  if (in != 0 && expected != (int)s.g.size()) bad(s, "a team of an incomplete count");
   if (members > 0 && (in == 0) != (offs == 1)) bad(s, "left without one member calling off");
 }
 
@@ -75,8 +76,9 @@ void walk(const State& s, int depth) {
 int main(int argc, char** argv) {
   const int grid = std::atoi(argv[1]), polls = std::atoi(argv[3]);
   members = std::atoi(argv[2]);
+  expected = grid + std::atoi(argv[4]);
   State s;
-  for (int i = 0; i < grid; ++i) s.g.emplace_back((uint32_t)grid, i < members, polls);
+  for (int i = 0; i < grid; ++i) s.g.emplace_back((uint32_t)expected, i < members, polls);
   walk(s, 0);
   std::printf("ok %zu\n", seen.size());
 }

@@ -40,3 +40,16 @@ def test_called_off_equals_oracle(no_teams, name):
                 np.testing.assert_array_equal(t.cpu().numpy().view(np.uint32), edist)
                 np.testing.assert_array_equal(r.cpu().numpy(), epred)
         g.free()
+
+
+def test_one_try_per_call(no_teams):
+    """The first team that cannot form is the last one that a call waits for; where teams form, they run the levels."""
+    hg = gg.add_weights(GRAPHS["path"](), seed=3)
+    for ctx, off in ((no_teams, True), (gr.Context(0), False)):
+        g = gr.Graph.from_host(ctx, hg, symmetric=True)
+        for kw in ({}, dict(graph_blocks=1)):
+            stats = [gr.bfs(g, 0, opts=gr.default_opts(**kw))[2]]
+            stats += [gr.sssp(g, [0], opts=gr.default_opts(sssp_delta=d, **kw))[2] for d in (0, 40)]
+            for st in stats:
+                assert st["team_levels"] == -1 if off else st["team_levels"] > st["iterations"] // 2, (kw, st)
+        g.free()

@@ -17,8 +17,10 @@ def model(tmp_path_factory):
     return exe
 
 
+@pytest.mark.parametrize("more", [0, 1])  # workgroups expected that never register
 @pytest.mark.parametrize("polls", [0, 1, 2])
 @pytest.mark.parametrize("grid,members", [(1, 1), (2, 2), (3, 1), (3, 2), (3, 3), (4, 2), (4, 3), (4, 4), (4, 0)])
-def test_every_interleaving_agrees(model, grid, members, polls):
-    r = subprocess.run([model, str(grid), str(members), str(polls)], capture_output=True, text=True, timeout=60)
+def test_every_interleaving_agrees(model, grid, members, polls, more):
+    r = subprocess.run([model, str(grid), str(members), str(polls), str(more)],
+                       capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
