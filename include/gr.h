@@ -109,7 +109,8 @@ typedef struct gr_level_trace {
                           4 pull TWC, 5 pull groups (either over the bitmap, or over the
                           short list of still-unvisited vertices the previous pull level
                           left), 6 step of a device block (step_us and
-                          kernel_us are then the block's time divided by its levels),
+                          kernel_us are then the block's time divided by its levels; a
+                          traced block is cut at 64 levels, each with a host round trip),
                           7 SSSP priority-queue refill (far pile split), 8 / 9 / 10 SSSP
                           TWC / LB_LIGHT / LB relaxation with the byte-mark filter (10:
                           also its form with the hubs' distance bounds in LDS),

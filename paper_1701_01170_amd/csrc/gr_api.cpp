@@ -846,8 +846,7 @@ gr_status dl_plan(gr_ctx* ctx, Arena& ar, const gr_graph* g, const gr_opts& o, b
   d->len = kDlFirstPairs;
   d->blocks = ctx->cu_count > 0 ? ctx->cu_count : 256;
   d->log = nullptr;
-  // (the block log's largest degrees come from the staged form)
-  d->log_w = tracing || g->max_degree > 8 ? -1 : g->max_degree > 4 ? 3 : 2;
+  d->log_w = g->max_degree > 8 ? -1 : g->max_degree > 4 ? 3 : 2;
   // A team of half as many members has a cheaper start and barrier, and enough lanes
   // for the frontiers of a mesh of kTeamHalfMaxV vertices (about its side, times 4 or 8
   // edge slots): BFS on a 300 x 200 grid 2.28 -> 1.94 ms, 1500 x 1500 15.1 -> 14.5, 2048

@@ -207,7 +207,8 @@ struct TeamWord {       // one per kernel of a block, zero at its start
   uint32_t q_count[3];  // append counters, rotating by level
   uint32_t pad1;
   unsigned long long arrive[3];  // arrivals | vertices << 8 | edges << 32, rotating by level
-  uint32_t pad2[4];
+  uint32_t max_deg[3];  // traced calls: largest degree of the frontier, rotating by level
+  uint32_t pad2;
 };
 static_assert(sizeof(TeamWord) == 64, "word size");
 static_assert(kTeamWords * sizeof(TeamWord) <= kStatsGrid * sizeof(int64_t),
@@ -329,6 +330,9 @@ __global__ __launch_bounds__(kAdvBlock) void k_team(DlArgs a, F f) {
                          __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(&tw->q_count[(it + 1) % 3], 0u, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
+      if (a.log)
+        __hip_atomic_store(&tw->max_deg[(it + 1) % 3], 0u, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
   };
   while (step < a.max_steps) {
@@ -391,7 +395,10 @@ __global__ __launch_bounds__(kAdvBlock) void k_team(DlArgs a, F f) {
         ++it;
       }
       total = m;
-      mx = 1 << a.log_w;  // (the log's largest degree: the graph's bound)
+      if (a.log) {  // traced: the largest degree over the team
+        mx = wave_max(d);
+        if (lane() == 0 && mx > 0) atomicMax(&tw->max_deg[it % 3], (uint32_t)mx);
+      }
       slots = nf << a.log_w;
       e0 = 0;
       e1 = slots;
@@ -442,11 +449,6 @@ __global__ __launch_bounds__(kAdvBlock) void k_team(DlArgs a, F f) {
     if (total > kTeamMaxM || total > a.max_m ||
         (a.do_a >= 0.0 && (double)total > pull_bound * a.do_a))
       break;
-    if (a.log && me == 0 && threadIdx.x == 0) {
-      a.log[3 * step + 0] = n;
-      a.log[3 * step + 1] = total;
-      a.log[3 * step + 2] = mx;
-    }
     // each frontier vertex once over the team
     if (sliced) {
       if ((int)threadIdx.x < nf) fs.frontier_vertex(s_u[threadIdx.x]);
@@ -515,6 +517,11 @@ __global__ __launch_bounds__(kAdvBlock) void k_team(DlArgs a, F f) {
     if (x == ~0ull) {
       failed = true;
       break;
+    }
+    if (a.log && me == 0 && threadIdx.x == 0) {
+      a.log[3 * step + 0] = n;
+      a.log[3 * step + 1] = total;
+      a.log[3 * step + 2] = sliced ? (int64_t)load_shared<true>(&tw->max_deg[it % 3]) : mx;
     }
     vm += total;
     vn += n;
