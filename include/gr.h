@@ -37,6 +37,13 @@
  *     (60 s, or GR_WAIT_LIMIT_MS from the environment when the context is
  *     created); past it they return GR_EHIP, and the context must then be
  *     destroyed, since its stream may still hold the unfinished work.
+ *   - A context keeps its working arrays from call to call.  Arrays that a call
+ *     can do without (gr_bfs_multi's depth planes and parent rows, 32 and up
+ *     to 256 bytes per vertex; gr_sssp_multi's distance bounds, 4 to 16) take
+ *     at most a sixteenth of the device's memory each, and are given back
+ *     where another array or a graph of the context finds no memory.
+ *     GR_WORKSPACE_LIMIT_KB from the environment, read when the context is
+ *     created, bounds all working arrays together (past it: GR_ENOMEM).
  *   - Small levels of gr_bfs / gr_sssp run on a team of workgroups that wait
  *     for one another; on a chip full of other work they give up after a
  *     bounded number of polls and the levels run without a team.

@@ -58,27 +58,76 @@ gr_status ws_address(int device, void** out) {
 }
 }  // namespace
 
+namespace {
+// Arrays that a call can do without (it then takes a slower path).
+constexpr Slot kOptionalSlots[] = {S_MS_PLANES, S_MS_PROW, S_MS_MIRROR};
+// Calls that go without an array once its memory was refused, before it is asked for again.
+constexpr int kOptionalRetry = 16;
+
+void pool_free(gr_ctx* ctx, DevBuf& b) {
+  if (b.ptr) (void)hipFree(b.ptr);
+  ctx->pool_bytes -= b.bytes;
+  b = DevBuf{};
+}
+
+hipError_t pool_alloc(gr_ctx* ctx, DevBuf& b, size_t bytes) {
+  hipError_t e = hipErrorOutOfMemory;
+  if (!ctx->pool_limit || ctx->pool_bytes + bytes <= ctx->pool_limit) e = hipMalloc(&b.ptr, bytes);
+  if (e != hipSuccess) {
+    b.ptr = nullptr;
+    (void)hipGetLastError();
+    return e;
+  }
+  b.bytes = bytes;
+  ctx->pool_bytes += bytes;
+  return e;
+}
+
+// Gives the optional arrays back; true if there were any.  (A call takes them after all
+// its other arrays, so none of them is in use when one of those is asked for.)
+bool drop_optional(gr_ctx* ctx) {
+  bool any = false;
+  for (Slot s : kOptionalSlots) {
+    any = any || ctx->pool[s].ptr;
+    pool_free(ctx, ctx->pool[s]);
+  }
+  return any;
+}
+
+size_t pool_rounded(size_t bytes) { return bytes + bytes / 8; }  // head-room so slowly growing requests do not thrash
+}  // namespace
+
 gr_status pool_get(gr_ctx* ctx, Slot s, size_t bytes, void** out) {
   DevBuf& b = ctx->pool[s];
   if (bytes == 0) bytes = 1;
   if (b.bytes < bytes) {
-    if (b.ptr) {
-      GR_HIP(hipFree(b.ptr));
-      b.ptr = nullptr;
-      b.bytes = 0;
-    }
-    size_t alloc = bytes + bytes / 8;  // head-room so slowly growing requests do not thrash
-    hipError_t e = hipMalloc(&b.ptr, alloc);
-    if (e != hipSuccess) {
-      b.ptr = nullptr;
-      (void)hipGetLastError();
+    pool_free(ctx, b);
+    const size_t alloc = pool_rounded(bytes);
+    hipError_t e = pool_alloc(ctx, b, alloc);
+    if (e != hipSuccess && drop_optional(ctx)) e = pool_alloc(ctx, b, alloc);
+    if (e != hipSuccess)
       return fail(GR_ENOMEM, "device allocation of " + std::to_string(alloc) + " bytes failed: " +
                                  hipGetErrorString(e));
-    }
-    b.bytes = alloc;
   }
   *out = b.ptr;
   return GR_OK;
+}
+
+// One of kOptionalSlots: null past the context's bound for such an array, or where the
+// memory is refused (then also for the next kOptionalRetry calls: a large allocation
+// that fails is not tried in every call).
+void* pool_optional(gr_ctx* ctx, Slot s, size_t bytes) {
+  DevBuf& b = ctx->pool[s];
+  if (b.ptr && b.bytes >= bytes) return b.ptr;
+  int& wait = ctx->optional_wait[s];
+  if (pool_rounded(bytes) > ctx->optional_limit) return nullptr;
+  if (wait > 0) {
+    --wait;
+    return nullptr;
+  }
+  pool_free(ctx, b);
+  if (pool_alloc(ctx, b, pool_rounded(bytes)) != hipSuccess) wait = kOptionalRetry;
+  return b.ptr;
 }
 
 namespace {
@@ -310,6 +359,9 @@ extern "C" gr_status gr_ctx_create(int32_t device, gr_ctx** out) {
     const long long ms = std::atoll(w);
     if (ms > 0) c->wait_limit = std::chrono::milliseconds(ms);
   }
+  c->optional_limit = prop.totalGlobalMem / 16;
+  if (const char* w = std::getenv("GR_WORKSPACE_LIMIT_KB"); w && *w)
+    c->pool_limit = (size_t)std::max(std::atoll(w), 0ll) << 10;
   c->team_polls = kTeamJoinPolls;
   if (const char* w = std::getenv("GR_TEAM_POLLS"); w && *w)
     c->team_polls = (int32_t)std::min(std::max(std::atoll(w), 0ll), 1ll << 24);
@@ -539,6 +591,11 @@ extern "C" gr_status gr_graph_from_csr(gr_ctx* ctx, int64_t V, int64_t E, const 
   g->E = E;
   g->flags = flags;
   gr_status s = ingest(ctx, g, R, C, W, device_input, static_cast<hipStream_t>(stream));
+  if (s == GR_ENOMEM && drop_optional(ctx)) {
+    (void)hipGetLastError();
+    free_graph_buffers(g);
+    s = ingest(ctx, g, R, C, W, device_input, static_cast<hipStream_t>(stream));
+  }
   if (s != GR_OK) {
     free_graph_buffers(g);
     delete g;
@@ -1698,9 +1755,10 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
   while ((1 << kp_log) < std::min<int32_t>(k, 64)) ++kp_log;
   u64* planes = nullptr;
   uint32_t* prow = nullptr;
-  if (pool_typed(ctx, S_MS_PLANES, (size_t)V * kMsPlanes, &planes) != GR_OK) planes = nullptr;
-  if (planes && parent && pool_typed(ctx, S_MS_PROW, (size_t)V << kp_log, &prow) != GR_OK)
-    planes = nullptr;
+  if (parent)
+    prow = static_cast<uint32_t*>(pool_optional(ctx, S_MS_PROW, sizeof(uint32_t) * ((size_t)V << kp_log)));
+  if (prow || !parent)
+    planes = static_cast<u64*>(pool_optional(ctx, S_MS_PLANES, sizeof(u64) * (size_t)V * kMsPlanes));
 
   GR_HIP(hipEventRecord(ctx->ev_start, st));
   GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(&ctrl->reached_edges), 2, 0u, st));
@@ -1991,9 +2049,8 @@ extern "C" gr_status gr_sssp_multi(gr_ctx* ctx, const gr_graph* g, const int32_t
   GR_TRY(pool_typed(ctx, S_CTRL, 1, &ctrl));
   GR_TRY(pool_typed(ctx, S_TMP0, 2 * kPass, &src_dev));
   // without room for the mirror every edge gathers its keys
-  void* mirror_p = nullptr;
-  if (pool_get(ctx, S_MS_MIRROR, (size_t)V * KSmax, &mirror_p) != GR_OK) mirror_p = nullptr;
-  const DistMirror mirror{static_cast<uint8_t*>(mirror_p), mirror_shift_for(g->max_weight)};
+  const DistMirror mirror{static_cast<uint8_t*>(pool_optional(ctx, S_MS_MIRROR, (size_t)V * KSmax)),
+                          mirror_shift_for(g->max_weight)};
   Ctrl* hc = ctx->host_ctrl;
   // q[cur]: the frontier; relax appends the improved vertices to q[cur + 1],
   // rotate lists those with an active source left in q[cur + 2], the next

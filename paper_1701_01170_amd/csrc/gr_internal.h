@@ -135,6 +135,11 @@ struct gr_ctx {
   int device = 0;
   int cu_count = 256;
   gr::DevBuf pool[gr::S_NSLOTS];
+  // Device memory the pool holds, the most it may (0: what the device has; environment
+  // GR_WORKSPACE_LIMIT_KB at context creation), the most for one array that a call can do
+  // without, and per such array the calls that still go without it after a refusal.
+  size_t pool_bytes = 0, pool_limit = 0, optional_limit = 0;
+  int optional_wait[gr::S_NSLOTS] = {};
   // Host view of the control block: coherent pinned host memory that a small
   // kernel fills (followed by a sequence number in publish_flag) after each
   // step, so the host polls memory instead of synchronising the stream.
