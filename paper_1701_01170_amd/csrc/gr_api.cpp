@@ -1879,7 +1879,6 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
           const int fi = fc ^ (i & 1);
           DlArgs da{g->R, g->C, q[qc], q[(qc + 1) % 3], qc, i, dl_max_n, dl_max_m, E, blk_do_a, V,
                     nullptr, ctrl};
-          da.edges_vs_all = 1;
           da.qs = Queues3{{qA, qB, qC}};
           da.cur0 = cur;
           da.seq = i;

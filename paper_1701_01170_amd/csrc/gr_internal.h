@@ -555,13 +555,13 @@ hipError_t launch_publish_select(const MlpSelect& m, Ctrl* ctrl, Ctrl* host_dst,
                                  uint32_t* host_flag, uint32_t seq, hipStream_t st,
                                  const PublishExtra& extra, const StatsSum& stats);
 
-// Device-predicated level blocks (iteration control): up to kDlMaxLevels
-// push levels are enqueued back to back; each level kernel first decides on
-// the device whether it may run (the previous level ran, the frontier is
-// non-empty and within max_n / max_m, and for BFS the direction heuristic
-// would still push), so the host reads the control block once per block
-// instead of once per level.  Each level appends to q[(cur + 1) % 3] and
-// clears the counters of q[(cur + 2) % 3], which nothing reads during it.
+// Device-predicated level blocks (iteration control): push levels are enqueued
+// back to back; each kernel first decides on the device whether it may run (the
+// previous level ran, the frontier is non-empty and within max_n / max_m, and
+// for the batched BFS the direction heuristic would still push), so the host
+// reads the control block once per block instead of once per level.  Each level
+// appends to q[(cur + 1) % 3] and clears the counters of q[(cur + 2) % 3], which
+// nothing reads during it.
 constexpr int kDlMaxN = 4096;        // frontier vertices staged in LDS per level
 constexpr int kTeamMaxM = 1 << 15;   // edges of a k_team level
 constexpr int kTeamMaxStaged = 2048; // vertices of one where every workgroup stages them all
@@ -570,7 +570,7 @@ constexpr int kTeamWords = 40;       // k_team kernels of one block
 constexpr int kBlockMaxSteps = 4096; // levels of one block (bounds the time of one kernel)
 constexpr int kDpMaxN = 1 << 16;     // frontier vertices of a k_dpush level (graphs without long rows)
 constexpr int kDpMaxDegree = 64;
-constexpr int kDlMaxLevels = 64;     // levels per block (log capacity)
+constexpr int kDlMaxLevels = 64;     // levels of a traced block (log capacity) and of a batched BFS's
 constexpr uint32_t kDlMaxRefill = 1u << 16;  // SSSP far-pile entries a block may split itself
 struct DlArgs {
   const int32_t* R;
@@ -581,11 +581,10 @@ struct DlArgs {
   int32_t step;               // level index inside the block
   int64_t max_n, max_m;       // run only while n_f <= max_n and m_f <= max_m
   int64_t E;                  // for the push -> pull test
-  double do_a;                // push -> pull when m_f > m_u * do_a (< 0: never)
+  double do_a;                // batched BFS: push -> pull when m_f > E * do_a (< 0: never)
   int64_t V;
   int64_t* log;               // [kDlMaxLevels][3]
   Ctrl* ctrl;
-  int32_t edges_vs_all = 0;   // 1: push -> pull when m_f > E * do_a (batched BFS's rule)
   // k_dstep and k_team: the queues, the block's first one, this kernel's place in
   // the block and the block's most levels (q_cur, q_next, cur, step: k_dpush);
   // k_team: its words [kTeamWords], the log2 of the edge slots per vertex where no

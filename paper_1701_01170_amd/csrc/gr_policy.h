@@ -49,7 +49,6 @@ struct Selector {
   bool sssp = false;
   bool learned = false;
   bool mode_pull = false;
-  int last_heuristic = -1;  // the heuristic's action at the last decide() (learned policy)
   uint64_t rng = 0;
   double avg_degree = 0.0;
 
@@ -99,9 +98,8 @@ struct Selector {
   // (the tail levels of a direction-optimised BFS stay in pull mode, since
   // m_f < m_u * do_b rarely holds once few vertices are left, and each would
   // cost a round trip for a few microseconds of work): such a level is
-  // pushed; the network may turn the heuristic's pull into a push, but not a
-  // push into a pull.  last_heuristic keeps the threshold rule's own answer,
-  // so that a block started against it keeps pushing.
+  // pushed, and so are the levels after it that fit the block; the network may
+  // turn the heuristic's pull into a push, but not a push into a pull.
   int decide(const LevelFeatures& lf, int device_choice = -1, const float* pred = nullptr,
              bool keep_push = false) {
     int a;
@@ -112,10 +110,8 @@ struct Selector {
     else if (o.policy == GR_POLICY_LEARNED && learned && device_choice >= 0 && pred) {
       a = (device_choice != h && pred[device_choice] + o.learned_margin < pred[h]) ? device_choice : h;
       if (keep_push && h < GR_PULL_TWC && a >= GR_PULL_TWC) a = h;
-      last_heuristic = raw;
     } else {
       a = h;
-      last_heuristic = raw;
     }
     if (!pull_ok && a >= GR_PULL_TWC) a -= 2;  // same balancing, push direction
     mode_pull = a >= GR_PULL_TWC;

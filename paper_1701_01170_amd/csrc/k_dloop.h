@@ -7,8 +7,8 @@
 // kernels, and stages the same frontier, so all take the same decision: the
 // level runs only if no earlier level of the block declined, the frontier is
 // non-empty, it fits the LDS staging (kDlMaxN vertices) and the caller's edge
-// bound, and (BFS) the direction heuristic of Sec. 5.1 would still push.  A
-// declining level sets dl_stop, so the rest of the block does nothing.
+// bound, and (batched BFS) the direction heuristic of Sec. 5.1 would still push.
+// A declining level sets dl_stop, so the rest of the block does nothing.
 //
 // A running level is output-balanced like LB (Sec. 5.1): each workgroup stages
 // the whole frontier in LDS, scans its degrees (which gives the level its m_f
@@ -121,12 +121,11 @@ __global__ __launch_bounds__(kAdvBlock) void k_dstep(DlArgs a, F f) {
   mx = wave_max(mx);
   if (lane() == 0) s_max[threadIdx.x / kWave] = mx;
   __syncthreads();
-  // the level runs only within the caller's edge bound and, under the
-  // heuristic, while its push test holds (Sec. 5.1 push -> pull); every
-  // workgroup computes the same total, so all take the same decision
+  // the level runs only within the caller's edge bound and (batched BFS) while
+  // the push test of Sec. 5.1 holds; every workgroup computes the same total, so
+  // all take the same decision
   bool run = total <= a.max_m;
-  const double pull_bound = a.edges_vs_all ? (double)a.E : (double)(a.E - vm - total);
-  if (run && a.do_a >= 0.0 && (double)total > pull_bound * a.do_a) run = false;
+  if (run && a.do_a >= 0.0 && (double)total > (double)a.E * a.do_a) run = false;
   if (!run) {
     if (lead) ctrl->dl_stop = 1;
     return;
@@ -445,10 +444,7 @@ __global__ __launch_bounds__(kAdvBlock) void k_team(DlArgs a, F f) {
       e1 = (int)(e0 + per < total ? e0 + per : total);
       slots = e1 - e0;
     }
-    const double pull_bound = a.edges_vs_all ? (double)a.E : (double)(a.E - vm - total);
-    if (total > kTeamMaxM || total > a.max_m ||
-        (a.do_a >= 0.0 && (double)total > pull_bound * a.do_a))
-      break;
+    if (total > kTeamMaxM || total > a.max_m) break;
     // each frontier vertex once over the team
     if (sliced) {
       if ((int)threadIdx.x < nf) fs.frontier_vertex(s_u[threadIdx.x]);
@@ -575,9 +571,8 @@ __global__ __launch_bounds__(kAdvBlock) void k_dpush(DlArgs a, F f) {
   const int64_t vn = ctrl->dl_vn[a.step & 1];
   const int next = (a.cur + 1) % 3, prev = (a.cur + 2) % 3;
   const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-  const double pull_bound = a.edges_vs_all ? (double)a.E : (double)(a.E - vm - m_f);
   if (!(n_f > 0 && n_f <= a.max_n && m_f <= a.max_m) ||
-      (a.do_a >= 0.0 && (double)m_f > pull_bound * a.do_a)) {
+      (a.do_a >= 0.0 && (double)m_f > (double)a.E * a.do_a)) {
     if (lead) ctrl->dl_stop = 1;
     return;
   }
