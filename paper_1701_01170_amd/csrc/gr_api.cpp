@@ -904,11 +904,15 @@ gr_status dl_plan(gr_ctx* ctx, Arena& ar, const gr_graph* g, const gr_opts& o, b
   d->blocks = ctx->cu_count > 0 ? ctx->cu_count : 256;
   d->log = nullptr;
   d->log_w = g->max_degree > 8 ? -1 : g->max_degree > 4 ? 3 : 2;
-  // A team of half as many members has a cheaper start and barrier, and enough lanes
-  // for the frontiers of a mesh of kTeamHalfMaxV vertices (about its side, times 4 or 8
-  // edge slots): BFS on a 300 x 200 grid 2.28 -> 1.94 ms, 1500 x 1500 15.1 -> 14.5, 2048
-  // x 2048 15.5 -> 15.6; SSSP 768 x 768 11.2 -> 10.8.  Uniform random graphs of 300 K
-  // vertices lose 2 %.
+  // A team of half as many members has a cheaper start and barrier; with frontiers of
+  // a thousand vertices and more the other half's lanes are worth that.  The frontier
+  // is what counts, and only the device knows it, so V stands in for it: of the meshes
+  // of up to kTeamHalfMaxV vertices only near-square ones are past the balance, by
+  // little.  BFS, half against full: 300 x 200 1.42 and 1.64 ms, 100 x 20000 60 and 68,
+  // 1500 x 1500 10.4 and 10.3, 2048 x 2048 15.7 and 15.2, 3000 x 3000 26.1 and 23.6; a
+  // long strip past the bound is misjudged (100 x 60000: 181 and 203).  SSSP alike: 300
+  // x 200 2.74 and 2.91 ms, 2048 x 2048 47.8 and 49.2.  Uniform random graphs of 300 K
+  // vertices lose 2 % with half.
   d->team_blocks = d->log_w >= 0 && g->V <= kTeamHalfMaxV ? (d->blocks + 1) / 2 : d->blocks;
   d->graph = o.graph_blocks == 1 && !tracing && !ar.fixed();
   if (d->on && tracing) GR_TRY(ar.get(S_DLOG, 3 * kDlMaxLevels, &d->log));
