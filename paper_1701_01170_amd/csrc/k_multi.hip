@@ -109,8 +109,12 @@ constexpr int kMsU = 8;                    // neighbours in flight per lane
 constexpr int kMsLaneMax = 64;             // rows up to this long: one lane
 constexpr int kMsWaveMax = 2048;           // ... up to this long: one wavefront
 constexpr int kMsHubBlock = 1024;          // longer: a workgroup of this many threads
-constexpr int kMsPullRuns = 4;             // vertices per thread of the lane tier
-constexpr int kMsWaveBatch = 8;            // rows a wavefront takes at a time
+// Vertices per thread of the lane tier; one in graphs of up to kMsPullSmall vertices, which
+// have too few workgroups otherwise (R-MAT 10, 64 sources: a level's lane and wavefront
+// tiers 50 + 38 us with four vertices and eight rows at a time, 18 + 8 with one).
+constexpr int kMsPullRuns = 4;
+constexpr int64_t kMsPullSmall = 1 << 18;
+constexpr int kMsWaveBatch = 8;            // most rows a wavefront takes at a time
 
 // Neighbours base + r * 64 + lane of a row ending at re, and the bits of nd in
 // their frontier masks.
@@ -148,6 +152,7 @@ __device__ __forceinline__ int32_t ms_first(const int32_t (&u)[kMsU], const u64 
 // 10.3 ms).  With touched null the level was pushed without parents: the rows are
 // scanned for the bits in next, only their parents are written.  This kernel scans the rows of up to kMsLaneMax neighbours, one lane
 // each, and lists the longer ones for the two kernels below.
+template <int K>
 __global__ __launch_bounds__(256) void k_ms_pull(int64_t V, const int32_t* __restrict__ R,
                                                  const int32_t* __restrict__ C,
                                                  const u64* __restrict__ front,
@@ -157,7 +162,6 @@ __global__ __launch_bounds__(256) void k_ms_pull(int64_t V, const int32_t* __res
                                                  int32_t* __restrict__ mid_q,
                                                  int32_t* __restrict__ hub_q,
                                                  uint32_t* __restrict__ n_big) {
-  constexpr int K = kMsPullRuns;
   const int64_t v0 = (int64_t)blockIdx.x * (256 * K) + threadIdx.x;
   u64 need[K];
   int32_t rb[K], re[K];
@@ -231,8 +235,9 @@ __global__ __launch_bounds__(256) void k_ms_pull(int64_t V, const int32_t* __res
 
 // Rows of kMsLaneMax + 1 .. kMsWaveMax neighbours: one wavefront each, 512
 // neighbours per step; lane s keeps source s's parent, so a row's parents leave
-// in one store.  kMsWaveBatch rows per turn (their bounds loaded together, one
-// append), wavefronts in a grid-stride loop over the listed rows.
+// in one store.  Up to kMsWaveBatch rows per turn (their bounds loaded together, one
+// append), as many as leave every wavefront some; wavefronts in a grid-stride loop over
+// the listed rows.
 __global__ __launch_bounds__(256) void k_ms_pull_mid(
     const int32_t* __restrict__ list, const uint32_t* __restrict__ n_list,
     const int32_t* __restrict__ R, const int32_t* __restrict__ C, const u64* __restrict__ front,
@@ -240,10 +245,11 @@ __global__ __launch_bounds__(256) void k_ms_pull_mid(
     uint32_t* __restrict__ n_touched, MsParents par) {
   constexpr int NW = 256 / kWave;
   const int64_t n = *n_list;
-  const int64_t stride = (int64_t)gridDim.x * NW * kMsWaveBatch;
-  for (int64_t i0 = ((int64_t)blockIdx.x * NW + threadIdx.x / kWave) * kMsWaveBatch; i0 < n;
-       i0 += stride) {
-    const int cnt = n - i0 < kMsWaveBatch ? (int)(n - i0) : kMsWaveBatch;
+  const int64_t waves = (int64_t)gridDim.x * NW;
+  const int batch = n <= waves ? 1 : n < waves * kMsWaveBatch ? (int)((n + waves - 1) / waves) : kMsWaveBatch;
+  for (int64_t i0 = ((int64_t)blockIdx.x * NW + threadIdx.x / kWave) * batch; i0 < n;
+       i0 += waves * batch) {
+    const int cnt = n - i0 < batch ? (int)(n - i0) : batch;
     int32_t lv = 0, lrb = 0, lre = 0;
     u64 lneed = 0;
     if (lane() < cnt) {
@@ -586,7 +592,9 @@ hipError_t launch_ms_pull(int64_t V, int64_t E, int64_t max_degree, const int32_
                           hipStream_t st) {
   const MsParents par = parents_of(o, V, perm);
   const bool mid = max_degree > kMsLaneMax, hub = max_degree > kMsWaveMax;
-  k_ms_pull<<<blocks_for(V, 256 * kMsPullRuns), 256, 0, st>>>(
+  const bool small = V <= kMsPullSmall;
+  const auto lane_tier = small ? k_ms_pull<1> : k_ms_pull<kMsPullRuns>;
+  lane_tier<<<blocks_for(V, small ? 256 : 256 * kMsPullRuns), 256, 0, st>>>(
       V, R, C, front, visit, full, next, touched, n_touched, par, mid ? mid_q : nullptr,
       hub ? hub_q : nullptr, n_big);
   // the hubs first: the longest rows of the level start earliest
@@ -597,7 +605,7 @@ hipError_t launch_ms_pull(int64_t V, int64_t E, int64_t max_degree, const int32_
   }
   if (mid) {
     const int64_t most = E / kMsLaneMax + 1;
-    const int64_t g = blocks_for(most < V ? most : V, 4 * kMsWaveBatch);
+    const int64_t g = blocks_for(most < V ? most : V, 4);
     k_ms_pull_mid<<<(unsigned)(g < 2048 ? g : 2048), 256, 0, st>>>(
         mid_q, &n_big[0], R, C, front, visit, full, next, touched, n_touched, par);
   }
