@@ -57,16 +57,34 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Appends v of the lanes with `first` to q: one counter atomic per wavefront.
-__device__ __forceinline__ void append_first(bool first, int32_t v, int32_t* __restrict__ q,
-                                             uint32_t* __restrict__ count) {
-  const uint64_t m = __ballot(first);
-  if (!m) return;
-  uint32_t base = 0;
-  if (lane() == 0) base = atomicAdd(count, (uint32_t)__popcll(m));
-  base = __shfl(base, 0);
-  if (first) q[base + (uint32_t)__popcll(m & ((1ull << lane()) - 1ull))] = v;
-}
+// A wavefront's entries for a list in memory, collected in LDS and appended with one
+// counter atomic per kCap - 64 or more of them: the counter is one address for the whole
+// grid and takes some 6.4 ns per atomic.  (A star's 1 M edges into the far pile: 82 us
+// with an atomic per 64 edges, 41 with these.)
+struct WaveList {
+  static constexpr int kCap = 256;
+  int32_t* buf;  // LDS [kCap], the wavefront's own
+  int n = 0;     // the same in all lanes
+  __device__ __forceinline__ void flush(int32_t* __restrict__ q, uint32_t* __restrict__ count) {
+    if (n == 0) return;
+    wave_lds_fence();
+    uint32_t base = 0;
+    if (lane() == 0) base = atomicAdd(count, (uint32_t)n);
+    base = __shfl(base, 0);
+    for (int i = lane(); i < n; i += kWave) q[base + i] = buf[i];
+    wave_lds_fence();
+    n = 0;
+  }
+  // v of the lanes with `first`; called by all lanes
+  __device__ __forceinline__ void put(bool first, int32_t v, int32_t* __restrict__ q,
+                                      uint32_t* __restrict__ count) {
+    const uint64_t m = __ballot(first);
+    if (!m) return;
+    if (first) buf[n + __popcll(m & ((1ull << lane()) - 1ull))] = v;
+    n += __popcll(m);
+    if (n > kCap - kWave) flush(q, count);
+  }
+};
 
 // A vertex's mirror row: one byte per source.
 template <int KS>
@@ -91,10 +109,10 @@ constexpr int kMsItems = 512;  // listed (edge, source) pairs a wavefront relaxe
 // that after the first few edges into a vertex only improvements read its keys.
 // The sources' distances of 256 segments are staged in LDS (16 KB, so that 7
 // workgroups share a CU).
-// LIST costs an atomic on one counter per wavefront and 64 edges, some 6.4 ns each:
-// 420 K of them held an iteration of 27 M edges at 2.7 ms.  Without, nmask itself is
-// the list.  R-MAT 20, 16 sources, the four large iterations: 14.3 ms as a pair per
-// lane, 12.0 with LIST, 2.4 without.
+// LIST costs atomics on one counter, some 6.4 ns each (WaveList): with one per wavefront
+// and 64 edges, 420 K of them held an iteration of 27 M edges at 2.7 ms.  Without, nmask
+// itself is the list.  R-MAT 20, 16 sources, the four large iterations: 14.3 ms as a
+// pair per lane, 12.0 with LIST (one per 64 edges), 2.4 without.
 template <int KS, bool PQ, bool LIST>
 __global__ __launch_bounds__(256) void k_msssp_relax(
     const int32_t* __restrict__ frontier, const int32_t* __restrict__ offsets,
@@ -118,7 +136,11 @@ __global__ __launch_bounds__(256) void k_msssp_relax(
   __shared__ __align__(16) uint32_t s_du[kMsSegs * KS];  // ~0: source not active
   __shared__ uint16_t s_item[WAVES][kMsItems];           // source << 6 | lane
   __shared__ uint32_t s_near[WAVES][kWave], s_far[WAVES][kWave];
+  __shared__ int32_t s_list[LIST ? WAVES * WaveList::kCap : 1];
+  __shared__ int32_t s_pile[PQ ? WAVES * WaveList::kCap : 1];
   const int wv = threadIdx.x / kWave;
+  WaveList near_l{LIST ? &s_list[wv * WaveList::kCap] : nullptr};
+  WaveList far_l{PQ ? &s_pile[wv * WaveList::kCap] : nullptr};
   const int c = blockIdx.x;
   const int64_t e0 = (int64_t)c * chunk;
   const int64_t e1 = e0 + chunk < m_f ? e0 + chunk : m_f;
@@ -254,17 +276,19 @@ __global__ __launch_bounds__(256) void k_msssp_relax(
         if (total == 0) continue;
         const uint32_t nb = s_near[wv][lane()];
         if constexpr (LIST)
-          append_first(nb != 0 && atomicOr(&nmask[v[r]], nb) == 0u, v[r], out_q, out_count);
+          near_l.put(nb != 0 && atomicOr(&nmask[v[r]], nb) == 0u, v[r], out_q, out_count);
         else if (nb) atomicOr(&nmask[v[r]], nb);
         if constexpr (PQ) {
           const uint32_t fb = s_far[wv][lane()];
-          append_first(fb != 0 && atomicOr(&fmask[v[r]], fb) == 0u, v[r], far_q, far_count);
+          far_l.put(fb != 0 && atomicOr(&fmask[v[r]], fb) == 0u, v[r], far_q, far_count);
         }
         wave_lds_fence();
       }
     }
     __syncthreads();
   }
+  if constexpr (LIST) near_l.flush(out_q, out_count);
+  if constexpr (PQ) far_l.flush(far_q, far_count);
 }
 
 // Far-pile split (priority queue): for every pile entry and every source bit
