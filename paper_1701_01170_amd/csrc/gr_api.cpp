@@ -2023,7 +2023,7 @@ extern "C" gr_status gr_sssp_multi(gr_ctx* ctx, const gr_graph* g, const int32_t
   // Iterations with at least V / kMsListDivisor frontier edges, and all of them in
   // graphs of kMsScanVertices, do not list the vertices they improve: the next frontier
   // is found by reading all masks, which also clears the old ones (two kernels instead
-  // of three; 1 M vertices: 25 us, while the list's appends take 6.4 ns per 64 edges).
+  // of three; 1 M vertices: 25 us).
   constexpr int64_t kMsListDivisor = 8;
   const int KSmax = msssp_row(std::min<int32_t>(k, kPass));
 

@@ -369,7 +369,8 @@ __global__ __launch_bounds__(256) void k_msssp_clear(const int32_t* __restrict__
 // KS lanes per vertex, so that the rows are read in whole lines, four rows in flight
 // per lane.  The appends share one counter (6.4 ns each): many vertices go in tiles
 // of 1024, a list or a small graph, which need workgroups more than fewer appends, in
-// tiles of 64 (16 K vertices: 15 us in tiles of 1024, 5 in tiles of 64).
+// tiles of 64 (16 K vertices: 15 us in tiles of 1024, 5 in tiles of 64), graphs between
+// in tiles of 256 (90 K vertices, 16 sources: 28 us in tiles of 1024, 11 in tiles of 256).
 template <int KS, bool LIST, int kMoveTile>
 __global__ __launch_bounds__(256) void k_msssp_move(const int32_t* __restrict__ q,
                                                     const uint32_t* __restrict__ n, int64_t V,
@@ -497,6 +498,8 @@ __global__ __launch_bounds__(64) void k_msssp_source_pred(const int32_t* __restr
   if (s < k) pred[(int64_t)s * V + src_orig[s]] = -1;
 }
 
+constexpr int64_t kMsMidVertices = 1 << 19;  // k_msssp_move: tiles of 256 up to here
+
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
 }  // namespace
@@ -568,15 +571,16 @@ hipError_t launch_msssp_rotate(const int32_t* cur_q, const uint32_t* cur_n, int6
     k_msssp_clear<<<blocks_for(max_cur, 256), 256, 0, st>>>(cur_q, cur_n, amask);
   const int64_t n = next_q ? max_next : V;
   if (n <= 0) return hipGetLastError();
-  const bool large = !next_q && n > kMsScanVertices;
-  unsigned g = blocks_for(n, large ? 1024 : 64);
+  const int tile = next_q || n <= kMsScanVertices ? 64 : n <= kMsMidVertices ? 256 : 1024;
+  unsigned g = blocks_for(n, tile);
   if (g > 4096) g = 4096;
 #define GR_MS_MOVE(LIST, TILE)                                                                  \
   GR_MS_ROW(KS, (k_msssp_move<R_, LIST, TILE><<<g, 256, 0, st>>>(next_q, next_n, V, amask, nmask, \
                                                                  keys, relaxed, out_q, out_count)))
   if (next_q) GR_MS_MOVE(true, 64)
-  else if (large) GR_MS_MOVE(false, 1024)
-  else GR_MS_MOVE(false, 64)
+  else if (tile == 64) GR_MS_MOVE(false, 64)
+  else if (tile == 256) GR_MS_MOVE(false, 256)
+  else GR_MS_MOVE(false, 1024)
 #undef GR_MS_MOVE
   return hipGetLastError();
 }
