@@ -466,6 +466,7 @@ __global__ __launch_bounds__(256) void k_msssp_finalize(const u64* __restrict__ 
     const ulonglong2* row = reinterpret_cast<const ulonglong2*>(keys + v * KS);
 #pragma unroll
     for (int j = 0; j < KS / 2; ++j) {
+      if (2 * j >= k) break;
       const ulonglong2 x = row[j];
       key[2 * j] = x.x;
       key[2 * j + 1] = x.y;
@@ -590,7 +591,7 @@ hipError_t launch_msssp_finalize(const u64* keys, int KS, int32_t k, const int32
                                  const int32_t* src_orig_dev, int64_t* reached_edges,
                                  hipStream_t st) {
   unsigned g = blocks_for(V, 256);
-  if (g > 2048) g = 2048;
+  if (g > 1024) g = 1024;  // one atomic per workgroup, all on one address
   GR_MS_ROW(KS, (k_msssp_finalize<R_><<<g, 256, 0, st>>>(keys, k, R, V, dist, pred, inv,
                                                          reached_edges)))
   if (pred) k_msssp_source_pred<<<1, 64, 0, st>>>(src_orig_dev, k, V, pred);
