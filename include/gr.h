@@ -382,9 +382,10 @@ gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* graph, const int32_t* source
  * device uint32[k][V] (required), pred: device int32[k][V] or NULL; row s
  * equals gr_sssp with the single source sources[s] (same definitions and
  * canonical predecessors).  Needs weights; GR_ERANGE as gr_sssp.  opts used:
- * lb_chunk (512, 1024 (default here) or 2048 edges per workgroup; other
- * values act as 1024), sssp_delta (> 0: near / far split of the improved
- * (vertex, source) pairs at one threshold for all sources, raised by delta
+ * lb_chunk (512, 1024 (default here) or 2048 edges per workgroup, other
+ * values act as 1024; fewer in iterations of few edges), sssp_delta (> 0:
+ * near / far split of the improved (vertex, source) pairs at one threshold for
+ * all sources, raised by delta
  * when the frontier runs dry; results unchanged) and max_iterations.  stats:
  * teps_edges summed over the sources; iterations of the longest pass;
  * inspected_edges = frontier edges swept (each once for all its sources). */

@@ -2025,6 +2025,19 @@ extern "C" gr_status gr_sssp_multi(gr_ctx* ctx, const gr_graph* g, const int32_t
   // is found by reading all masks, which also clears the old ones (two kernels instead
   // of three; 1 M vertices: 25 us).
   constexpr int64_t kMsListDivisor = 8;
+  // Edges per workgroup of an iteration: at most `chunk`, halved while the iteration's m_f
+  // edges give fewer than kMsGroups workgroups, one per CU: a workgroup works through its
+  // edges 512 at a time, and with 1024 a small frontier leaves most CUs idle while a few
+  // take two turns (300 x 300 grid, 16 sources, 9.7 K edges an iteration: 31 ms with
+  // 1024, 23 with 256, 24 with 128; near / far 62 and 46).  The map of chunk starts has
+  // room for E / 512 + 2 of them.
+  constexpr int kMsMinChunk = 256;
+  constexpr int64_t kMsGroups = 256;
+  auto chunk_for = [&](int64_t m_f) {
+    int c = chunk;
+    while (c > kMsMinChunk && m_f < c * kMsGroups && m_f / (c / 2) + 1 <= E / 512 + 2) c /= 2;
+    return c;
+  };
   const int KSmax = msssp_row(std::min<int32_t>(k, kPass));
 
   unsigned long long* keys;
@@ -2101,13 +2114,14 @@ extern "C" gr_status gr_sssp_multi(gr_ctx* ctx, const gr_graph* g, const int32_t
         T = T1;
         pile ^= 1;
       } else {
+        const int ch = chunk_for(m_f);
         GR_HIP(launch_frontier_offsets(q[cur], n_f, g->R, bsums, offsets, rstart,
-                                       chunks, chunk, st));
+                                       chunks, ch, st));
         const MsFar far{fmask, use_pq ? piles + (int64_t)pile * V : nullptr, &ctrl->far_count[pile],
                         T};
         const int q1 = (cur + 1) % 3, q2 = (cur + 2) % 3;
         int32_t* list = m_f >= V / kMsListDivisor || V <= kMsScanVertices ? nullptr : q[q1];
-        GR_HIP(launch_msssp_relax(KS, chunk, q[cur], offsets, rstart, chunks, n_f, m_f, g->C, g->W,
+        GR_HIP(launch_msssp_relax(KS, ch, q[cur], offsets, rstart, chunks, n_f, m_f, g->C, g->W,
                                   keys, mirror, amask, nmask, use_pq ? &far : nullptr, g->perm,
                                   relaxed, list, &ctrl->q_count[q1], st));
         GR_HIP(launch_msssp_rotate(q[cur], &ctrl->q_count[cur], n_f, list, &ctrl->q_count[q1],
