@@ -94,7 +94,8 @@ bool drop_optional(gr_ctx* ctx) {
   return any;
 }
 
-size_t pool_rounded(size_t bytes) { return bytes + bytes / 8; }  // head-room so slowly growing requests do not thrash
+// With head-room, so that slowly growing requests do not thrash.
+size_t pool_rounded(size_t bytes) { return bytes + bytes / 8; }
 }  // namespace
 
 gr_status pool_get(gr_ctx* ctx, Slot s, size_t bytes, void** out) {
@@ -253,11 +254,11 @@ gr_status read_ctrl(gr_ctx* ctx, Ctrl* dev, hipStream_t st, const StatsSum& stat
 // Edges per workgroup of output-balanced LB where the caller leaves it to the
 // library (lb_chunk = 0).  BFS expansions gain from long chunks (32 edges in
 // flight per lane) as long as enough workgroups remain to fill the chip: the
-// largest size that still gives kLbGroups of them, four per CU.  The passes whose edges each gather an 8-byte value (SSSP, BC) run best with 1024
-// edges at every size (with 8192 a frontier of 197 K edges is 25 workgroups on
-// 256 CUs: directed uniform graph of 300 K vertices, SSSP 1.81 ms against
-// 1.18 ms), and their degree scan is queued before the host knows the
-// frontier's size.
+// largest size that still gives kLbGroups of them, four per CU.  The passes whose
+// edges each gather an 8-byte value (SSSP, BC) run best with 1024 edges at every
+// size (with 8192 a frontier of 197 K edges is 25 workgroups on 256 CUs: directed
+// uniform graph of 300 K vertices, SSSP 1.81 ms against 1.18 ms), and their degree
+// scan is queued before the host knows the frontier's size.
 constexpr int kBfsChunk = 8192;
 constexpr int kGatherChunk = 1024;
 constexpr int kMinChunk = 512;
@@ -1760,9 +1761,11 @@ extern "C" gr_status gr_bfs_multi(gr_ctx* ctx, const gr_graph* g, const int32_t*
   u64* planes = nullptr;
   uint32_t* prow = nullptr;
   if (parent)
-    prow = static_cast<uint32_t*>(pool_optional(ctx, S_MS_PROW, sizeof(uint32_t) * ((size_t)V << kp_log)));
+    prow = static_cast<uint32_t*>(
+        pool_optional(ctx, S_MS_PROW, sizeof(uint32_t) * ((size_t)V << kp_log)));
   if (prow || !parent)
-    planes = static_cast<u64*>(pool_optional(ctx, S_MS_PLANES, sizeof(u64) * (size_t)V * kMsPlanes));
+    planes = static_cast<u64*>(
+        pool_optional(ctx, S_MS_PLANES, sizeof(u64) * (size_t)V * kMsPlanes));
 
   GR_HIP(hipEventRecord(ctx->ev_start, st));
   GR_HIP(launch_fill_u32(reinterpret_cast<uint32_t*>(&ctrl->reached_edges), 2, 0u, st));

@@ -192,8 +192,9 @@ __global__ __launch_bounds__(kAdvBlock) void k_dstep(DlArgs a, F f) {
 // the total of workgroups seen (team_join.h); when all have been seen, all members run
 // at the same time and know their number.  If that takes too long (the chip is full of
 // other work) the first to give up calls the run off for all of them, the block's other
-// kernels do the levels, and the rest of the call runs without teams.  One workgroup alone has the same latency per trip, but its CU's
-// throughput bounds levels of more than some 2 K edges (6.7 K edges: 32 us).
+// kernels do the levels, and the rest of the call runs without teams.  One workgroup
+// alone has the same latency per trip, but its CU's throughput bounds levels of more
+// than some 2 K edges (6.7 K edges: 32 us).
 //
 // Rows of at most 8 (a.log_w >= 0): a workgroup takes an equal slice of the
 // frontier with 1 << log_w edge slots per vertex.  Other graphs: every workgroup

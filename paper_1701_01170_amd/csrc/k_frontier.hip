@@ -59,9 +59,9 @@ __device__ __forceinline__ int64_t slice_len(int64_t n_f, int G) {
 // dependent loads, 4-6 us up to 200 K entries.)  With deg / rstart (nullable)
 // every entry's degree and row start are kept for the degree scan, which then
 // streams them instead of gathering the row offsets again (2.06 M entries of an
-// R-MAT 22 SSSP, both kernels: 60 -> 45 us; 177 K entries: 24 -> 12 us).  With bm the visited bitmap's words are merged on the
-// way (live |= old, see k_bfs.hip), which needs no launch of its own then.
-// Block 0 clears the two counters the next step appends to.
+// R-MAT 22 SSSP, both kernels: 60 -> 45 us; 177 K entries: 24 -> 12 us).  With bm the
+// visited bitmap's words are merged on the way (live |= old, see k_bfs.hip), which
+// needs no launch of its own then.  Block 0 clears the two counters the next step appends to.
 __device__ __forceinline__ void frontier_stats(const int32_t* __restrict__ frontier, int64_t n_f,
                                                const int32_t* __restrict__ R,
                                                int64_t* __restrict__ block_sums,

@@ -150,8 +150,9 @@ __device__ __forceinline__ int32_t ms_first(const int32_t (&u)[kMsU], const u64 
 // wavefront that owns the vertex, the first 64 vertices of a degree-ordered
 // graph shared one wavefront (R-MAT 20, 64 sources: 10.2 ms of a level's
 // 10.3 ms).  With touched null the level was pushed without parents: the rows are
-// scanned for the bits in next, only their parents are written.  This kernel scans the rows of up to kMsLaneMax neighbours, one lane
-// each, and lists the longer ones for the two kernels below.
+// scanned for the bits in next, only their parents are written.  This kernel scans
+// the rows of up to kMsLaneMax neighbours, one lane each, and lists the longer ones
+// for the two kernels below.
 template <int K>
 __global__ __launch_bounds__(256) void k_ms_pull(int64_t V, const int32_t* __restrict__ R,
                                                  const int32_t* __restrict__ C,
